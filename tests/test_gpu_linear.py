@@ -188,3 +188,17 @@ def test_linear_full_size(name, m_sub):
     sa_full = np.zeros(M, np.float32)
     a8_full[rows], sa_full[rows] = a8, sa_
     check_linear(y, a8_full, sa_full, w8, sw_, b, f"{name} linear", rows)
+
+
+@pytest.mark.parametrize("M,N,K,bias,pad_y", [
+    (1, 40, 256, True, 0),        # 32 x 32 tiles: 2 slices for 4 waves, ragged channels
+    (33, 5120, 640, True, 8),     # 32 x 64 tiles: 5 slices, waves of 2 and 1
+    (127, 5128, 1152, False, 0),  # 64 x 64 tiles: 9 slices, ragged in both
+    (300, 8960, 256, True, 0),    # 128 x 128 tiles, 2 stages (fewer than the ring holds)
+    (300, 8968, 896, False, 24),  # 128 x 128 tiles, 7 stages, ragged in both
+])
+def test_linear_few_tokens(M, N, K, bias, pad_y):
+    """Each tile size of the small-M dispatch at its edges: partial tiles,
+    fewer K slices than waves or ring slots, odd slice counts."""
+    y, a8, sa_, w8, sw, b = linear_case(M, N, K, seed=M + N + K, bias=bias, pad_y=pad_y)
+    check_linear(y, a8, sa_, w8, sw, b, f"linear M{M} N{N} K{K}")
