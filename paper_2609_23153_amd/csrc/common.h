@@ -79,24 +79,15 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return f32_to_bf16_rne(lo) | (f32_to_bf16_rne(hi) << 16);
 }
 
-// OCP e4m3fn code of y for |y| < 464 (callers scale so that |y| <= 448, up
-// to one fp32 rounding): nearest value, ties to even, sign bit kept (so -0
-// and tiny negatives give 0x80).  Integer arithmetic on the fp32 fields.
-__device__ __forceinline__ uint32_t e4m3_rne(float y) {
-  const uint32_t u = __float_as_uint(y);
-  const uint32_t sign = (u >> 24) & 0x80u;
-  const uint32_t a = u & 0x7fffffffu;
-  uint32_t code;
-  if (a < 0x3c800000u) {  // |y| < 2^-6: e4m3 subnormal grid of step 2^-9
-    code = (uint32_t)__builtin_rintf(__uint_as_float(a) * 512.f);  // 0 .. 8
-  } else {
-    const uint32_t e = a >> 23;          // fp32 biased exponent (>= 121)
-    const uint32_t m3 = (a >> 20) & 7u;  // top 3 mantissa bits
-    const uint32_t rem = a & 0xfffffu;
-    const uint32_t up = (rem > 0x80000u) || (rem == 0x80000u && (m3 & 1u));
-    code = (((e - 120u) << 3) | m3) + up;  // e4m3 exponent bias 7 = fp32 bias 127 - 120
-  }
-  return sign | code;
+// OCP e4m3fn codes of the four bf16 values packed in (w0, w1), each times
+// inv in fp32 (callers scale so that every product is within 448, up to one
+// fp32 rounding): nearest value, ties to even, sign bit kept (-0 and tiny
+// negatives give 0x80).  v_cvt_pk_fp8_f32 gives these codes for every fp32
+// below 464 in magnitude (all of them compared with the integer rounding of
+// the fp32 fields), in 2 instructions where that rounding takes about 60.
+__device__ __forceinline__ uint32_t e4m3x4(uint32_t w0, uint32_t w1, float inv) {
+  const int o = __builtin_amdgcn_cvt_pk_fp8_f32(bf16_lo(w0) * inv, bf16_hi(w0) * inv, 0, false);
+  return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(bf16_lo(w1) * inv, bf16_hi(w1) * inv, o, true);
 }
 
 // Whole-wave reductions through DPP-free cross-lane shuffles.

@@ -4,8 +4,8 @@
 //   y[m][n] = (sum_k xq[m][k] * wq[n][k]) * sx[m] * sw[n] + bias[n]
 // runs on the fp8 matrix cores with fp32 accumulation and a bf16 output.
 //
-// Row quantisation: one wavefront per row, the whole row held in registers
-// (16-byte chunks), the absolute maximum reduced with integer compares on the
+// Row quantisation: one workgroup (or, for short rows, one wavefront) per row,
+// the whole row held in registers (16-byte chunks), the absolute maximum reduced with integer compares on the
 // bf16 magnitude bits; a = max(amax, 2^-100), scale = a / 448 and
 // codes = e4m3(x * (448 / a)), each quotient and product a correctly rounded
 // fp32 operation, the code rounded to nearest with ties to even.
@@ -41,24 +41,32 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
 
 // ---- per-row quantisation --------------------------------------------------
 
-constexpr int kRowsPerGroup = 4;  // one row per wave
+constexpr int kRowsPerGroup = 4;   // one row per wave
+constexpr int kFewRows = 1024;
 
-template <int P>  // 16-byte chunks per lane: rows of up to 512 * P elements
+// W waves per row, P 16-byte chunks per lane: rows of up to 512 * W * P
+// elements.  Bound by HBM when there are many rows (5120 columns x 75,600
+// rows: 198 us, 5.9 TB/s; one wave per row 214, and 226 with the codes rounded
+// in integer arithmetic) and by one row's chain of loads, maximum and
+// conversions when there are few (512 rows: 9.6 -> 2.9 us), which four waves
+// shorten.
+template <int P, int W>
 __global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t* __restrict__ x,
                                                          int64_t ldx, int64_t rows, int cols,
                                                          uint8_t* __restrict__ q,
                                                          float* __restrict__ scale) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * kRowsPerGroup + wave;
-  if (row >= rows) return;  // whole wave; no barrier below
+  const int64_t row = W == 1 ? (int64_t)blockIdx.x * kRowsPerGroup + wave : blockIdx.x;
+  if (W == 1 && row >= rows) return;  // whole wave; no barrier below
   const uint16_t* src = x + row * ldx;
   const int nch = cols >> 3;
+  const int c0 = W == 1 ? lane : (int)threadIdx.x;
 
   u32x4 v[P];
   uint32_t amax = 0;  // bf16 magnitude bits: integer order is value order
 #pragma unroll
   for (int p = 0; p < P; ++p) {
-    const int c = lane + kWave * p;
+    const int c = c0 + kWave * W * p;
     if (c < nch) {
       v[p] = ld16(src + 8 * c);
 #pragma unroll
@@ -70,22 +78,24 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t* __restr
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, o, kWave));
+  if (W > 1) {
+    __shared__ uint32_t red[4];
+    if (lane == 0) red[wave] = amax;
+    __syncthreads();
+    amax = max(max(red[0], red[1]), max(red[2], red[3]));
+  }
   const float a = fmaxf(__uint_as_float(amax << 16), 0x1p-100f);
   const float inv = __fdiv_rn(448.f, a);
-  if (lane == 0) scale[row] = __fdiv_rn(a, 448.f);
+  if (c0 == 0) scale[row] = __fdiv_rn(a, 448.f);
 
   uint8_t* dst = q + row * (int64_t)cols;
 #pragma unroll
   for (int p = 0; p < P; ++p) {
-    const int c = lane + kWave * p;
+    const int c = c0 + kWave * W * p;
     if (c < nch) {
       u32x2 out;
 #pragma unroll
-      for (int hw = 0; hw < 2; ++hw) {
-        const uint32_t w0 = v[p][2 * hw], w1 = v[p][2 * hw + 1];
-        out[hw] = e4m3_rne(bf16_lo(w0) * inv) | (e4m3_rne(bf16_hi(w0) * inv) << 8) |
-                  (e4m3_rne(bf16_lo(w1) * inv) << 16) | (e4m3_rne(bf16_hi(w1) * inv) << 24);
-      }
+      for (int hw = 0; hw < 2; ++hw) out[hw] = e4m3x4(v[p][2 * hw], v[p][2 * hw + 1], inv);
       *reinterpret_cast<u32x2*>(dst + 8 * c) = out;
     }
   }
@@ -121,11 +131,8 @@ __global__ __launch_bounds__(256) void quant_rows_stream_kernel(const uint16_t* 
     const u32x4 v = ld16(src + 8 * c);
     u32x2 out;
 #pragma unroll
-    for (int hw = 0; hw < 2; ++hw) {
-      const uint32_t w0 = v[2 * hw], w1 = v[2 * hw + 1];
-      out[hw] = e4m3_rne(bf16_lo(w0) * inv) | (e4m3_rne(bf16_hi(w0) * inv) << 8) |
-                (e4m3_rne(bf16_lo(w1) * inv) << 16) | (e4m3_rne(bf16_hi(w1) * inv) << 24);
-    }
+    for (int hw = 0; hw < 2; ++hw)
+      out[hw] = e4m3x4(v[2 * hw], v[2 * hw + 1], inv);
     *reinterpret_cast<u32x2*>(dst + 8 * c) = out;
   }
 }
@@ -825,14 +832,16 @@ hipError_t launch_quant_rows_fp8(const void* x, int64_t ldx, int64_t rows, int c
   const dim3 grid((unsigned)((rows + kRowsPerGroup - 1) / kRowsPerGroup));
   const uint16_t* xp = static_cast<const uint16_t*>(x);
   const int nch = cols / 8;
-  if (nch <= 64 * 4)
-    quant_rows_kernel<4><<<grid, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
-  else if (nch <= 64 * 10)
-    quant_rows_kernel<10><<<grid, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
-  else if (nch <= 64 * 16)
-    quant_rows_kernel<16><<<grid, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
-  else if (nch <= 64 * 28)
-    quant_rows_kernel<28><<<grid, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
+  // One row per workgroup, except for short rows in numbers that fill the chip
+  // (us, one wave per row / four: 1536 columns x 512 rows 3.0 / 2.4, x 2048
+  // 3.0 / 3.3; 5120 columns x 2048 rows 6.6 / 5.4, x 75,600 214 / 198).
+  const dim3 one((unsigned)rows);
+  if (nch <= 64 * 4 && (rows > kFewRows || nch <= 64))
+    quant_rows_kernel<4, 1><<<grid, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
+  else if (nch <= 256 * 3)
+    quant_rows_kernel<3, 4><<<one, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
+  else if (nch <= 256 * 8)
+    quant_rows_kernel<8, 4><<<one, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
   else
     quant_rows_stream_kernel<<<grid, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
   return hipGetLastError();

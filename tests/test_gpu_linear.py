@@ -202,3 +202,18 @@ def test_linear_few_tokens(M, N, K, bias, pad_y):
     fewer K slices than waves or ring slots, odd slice counts."""
     y, a8, sa_, w8, sw, b = linear_case(M, N, K, seed=M + N + K, bias=bias, pad_y=pad_y)
     check_linear(y, a8, sa_, w8, sw, b, f"linear M{M} N{N} K{K}")
+
+
+@pytest.mark.parametrize("rows,cols,pad", [
+    (1025, 2048, 0),     # short rows, more than 1024: one wave per row
+    (1024, 2048, 8),     # the same width, few rows: one workgroup per row
+    (3, 512, 0),         # one chunk per lane of one wave
+    (3, 520, 0),         # one chunk more: one workgroup per row
+    (5, 6152, 0),        # one chunk beyond three per lane
+    (2, 16384, 0),       # the widest row held in registers
+    (2, 16392, 8),       # the narrowest two-pass row
+])
+def test_quant_rows_dispatch_edges(rows, cols, pad):
+    x, _, _ = W.linear_inputs(rows, cols, 4, seed=rows + cols)
+    q, s = quant_gpu(x, pad)
+    check_quant(x, q, s, f"quant {rows}x{cols} pad {pad}")
