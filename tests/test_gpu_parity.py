@@ -153,6 +153,49 @@ def test_select_on_chip_capacity_edges(nb):
     select_and_check(q, k, 64, 300, f"nb={nb}")
 
 
+@pytest.mark.parametrize("H,N,block,keep_bp", [
+    (1, 2384 * 64 - 17, 64, 300),    # the longest on-chip row, 72 kept (more than a wave holds)
+    (1, 2385 * 64 - 17, 64, 100),    # one block more: the fp64 score matrix
+    (1, 1300 * 64, 64, 4000),        # the long rows' kernel, 520 of 1300 kept
+    (9, 8 * 64 + 1, 64, 5000),       # 8 rows a workgroup, a lone block in the last
+    (40, 100 * 128 - 5, 128, 7000),  # 32 rows a workgroup, 70 of 100 kept
+    (13, 700 * 64 - 1, 64, 1500),    # 16 rows a workgroup, 105 of 700 kept
+])
+def test_select_workgroup_sizes(H, N, block, keep_bp):
+    """Each workgroup size of the fused selection, with more blocks kept than
+    a wave has lanes (the whole-row search) and fewer."""
+    g = torch.Generator().manual_seed(N + H)
+    q = torch.randn(1, H, N, 128, generator=g).to(torch.bfloat16)
+    k = torch.randn(1, H, N, 128, generator=g).to(torch.bfloat16)
+    select_and_check(q, k, block, keep_bp, f"H={H} N={N} b={block} keep={keep_bp}")
+
+
+def test_select_whole_row_ties():
+    """More than 64 kept of key blocks that repeat in groups: the whole-row
+    search ends on a tied key, with the k-th place inside its group."""
+    g = torch.Generator().manual_seed(17)
+    k = torch.randn(1, 1, 40 * 64, 128, generator=g).to(torch.bfloat16).repeat(1, 1, 8, 1)
+    q = torch.randn(1, 1, 320 * 64, 128, generator=g).to(torch.bfloat16)
+    for keep in (2500, 6100):  # k = 80 (a whole number of groups), 196 (not)
+        select_and_check(q, k, 64, keep, f"period-40 key blocks keep={keep}")
+
+
+@pytest.mark.parametrize("B,H,N,block", [
+    (1, 1, 100, 64),       # two tiles
+    (2, 3, 16448, 128),    # two chunks, an odd tile count per head
+    (2, 40, 78592, 64),    # 98,240 tiles: the largest single launch
+    (2, 40, 78720, 64),    # 98,400: three launches
+])
+def test_schedule_launch_forms(B, H, N, block):
+    nb = -(-N // block)
+    g = torch.Generator().manual_seed(N)
+    for cnt in (torch.full((B, H, nb), 7, dtype=torch.int32),
+                torch.randint(0, 300, (B, H, nb), generator=g, dtype=torch.int32)):
+        order = sa.sparse_attn_schedule(cnt.to(DEV), N, 250, block=block)
+        torch.cuda.synchronize()
+        check_launch_order(order.cpu().numpy(), cnt.numpy(), 250, N, block, f"{B} {H} {N} {block}")
+
+
 @pytest.mark.parametrize("N,block", [(4160, 128), (1000, 64)])
 def test_select_token_major_batched(N, block):
     """Token-major [B, L, H, d] views with two batches: the fused kernel's
