@@ -116,10 +116,10 @@ int32_t sparse_attn_keep_count(int32_t keep_bp, int32_t nkb);
 /* Bytes of device workspace that `op` needs for this problem; `kmax` is the
  * row stride of the index list (ignored for SA_OP_SELECT and
  * SA_OP_SELECT_HEAD).  Returns 0 for an invalid descriptor or op.
- * Row-mode selection with nkb <= 1192 keeps the block scores on chip and
- * needs B*H*(2048*nkb + 16384*ceil(nkb/32) + 4*nkb) bytes; above that, and
- * in the whole-head mode, the fp64 score matrix (8*nkb^2 bytes per head) is
- * part of it. */
+ * Row-mode selection with nkb <= 1192 needs
+ * B*H*(2048*nkb + 16384*ceil(nkb/32) + 4*nkb) bytes; above that, and in the
+ * whole-head mode, room for the fp64 score matrix (8*nkb^2 bytes per head) is
+ * part of it.  (Row mode keeps the block scores on chip up to nkb = 2384.) */
 size_t sparse_attn_workspace_size(const sparse_attn_desc* desc, int32_t op, int32_t kmax);
 
 /*
@@ -127,7 +127,7 @@ size_t sparse_attn_workspace_size(const sparse_attn_desc* desc, int32_t op, int3
  * selection in BF16, so it reads the bf16 Q and K).
  *   score s_ij = (sum_{t in I_i} q_t) . (sum_{u in J_j} k_u) / (n_i n_j),
  * the mean unscaled logit of block (i, j), pooled and dotted in fp64.  The
- * row mode with nkb <= 1192 ranks bf16-matrix-core approximations of the
+ * row mode with nkb <= 2384 ranks bf16-matrix-core approximations of the
  * scores whose error is bounded, and rescores in fp64 the blocks whose bound
  * reaches across the k-th score, so its lists are those of the fp64 scores.
  *  q, k    bf16 [B][H][L][d] via desc strides (o_stride and v_stride unused)

@@ -6,8 +6,8 @@
 //   pool   : Q and K streamed once from HBM; per block, the fp64 sum of the
 //            bf16 token vectors (exact for bf16 inputs whose exponents span
 //            fewer than ~38 binades, so it does not depend on summation order)
-//   row mode, nb <= kFStrideBig (the scores never reach HBM): pool of K only,
-//   score_topk : per 32 query blocks, their pooling (same arithmetic as the
+//   row mode, nb <= kFStrideLong (the scores never reach HBM): pool of K only,
+//   score_topk : per 8 to 32 query blocks, their pooling (same arithmetic as the
 //            pool launch), then approximate scores of every key block
 //            on the bf16 matrix cores from a two-term bf16 split of the
 //            pooled sums, kept in LDS; per query block the k-th largest
@@ -98,10 +98,10 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
   return add_swapped<false>(x);
 }
 
-// Fused row selection: query blocks per workgroup, and the 16-deep k-steps of
+// Fused row selection: key blocks per operand tile, and the 16-deep k-steps of
 // the split operands (steps 0..7: high parts of channels 16 s .. 16 s + 15,
 // steps 8..15: low parts of the same channels).
-constexpr int kFRows = 32;
+constexpr int kKTile = 32;
 constexpr int kFSteps = 16;
 
 // Smallest fp32 >= x (x >= 0 or NaN).
@@ -379,6 +379,18 @@ __device__ __forceinline__ uint32_t kth_largest32(const uint32_t (&v)[KPL], cons
   return prefix;
 }
 
+// Whole-wave sum, in every lane (a wave-uniform value).
+__device__ __forceinline__ int wave_sum_u32(int x) {
+  x += (int)row_ror<8>((uint32_t)x, 0u);
+  x += (int)row_ror<4>((uint32_t)x, 0u);
+  x += (int)row_ror<2>((uint32_t)x, 0u);
+  x += (int)row_ror<1>((uint32_t)x, 0u);
+  const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
+  x = (int)(a[0] + a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+  return __builtin_amdgcn_readfirstlane((int)(b[0] + b[1]));
+}
+
 // The k largest of the wave's member keys (hi, lo words; ties to the lower
 // index jj), written to out in ascending jj order.  Members must sit in
 // ascending jj order over (slot t, lane).  Requires 1 <= k <= count(member).
@@ -545,8 +557,17 @@ hipError_t launch_topk_any(const double* scores, int nb, int rows, int k, int km
 }
 
 // ---- fused score + top-k (row mode) ---------------------------------------
-// One workgroup of 8 waves per 32 query blocks of a (batch, head); scores for
-// all nb key blocks stay in LDS as order-preserving 32-bit keys.
+// One workgroup of 8 waves per ROWS query blocks of a (batch, head); scores for
+// all nb key blocks stay in LDS as order-preserving 32-bit keys, in rows of
+// NBP.  A CU holds one such workgroup (its waves take the register file), and
+// its phases (pooling, products, one row after another) are chains of
+// latencies: one of 32, 16 or 8 rows takes about 5, 3 or 2 units of 10 us, and
+// the launch takes the size whose rounds over the CUs cost least (us, pool
+// included, 32 / 16 / 8 rows: 2 heads x 64 blocks 36 / 23 / 16, 5 x 512 57 / 40
+// / 44, 5 x 1182 72 / 82 / 83, 10 x 1182 149 / 143 / 166, 40 x 1182 479 / 518 /
+// 608), although fewer rows leave part of the products' tile unused.  16 rows
+// also fit up to 2384 key blocks: 5 heads x 1744 at 5% take 194 us, against 246
+// for the fp64 score matrix and its top-k.
 //
 // Approximation.  With the pooled sums split as q = q1 + q2 + rq and
 // k = k1 + k2 + rk (bf16 parts from the pooling, |rq| <= 2^-16 |q| (1 + 2^-14)
@@ -579,8 +600,9 @@ hipError_t launch_topk_any(const double* scores, int nb, int rows, int k, int km
 // and the selection of the unfused kernel run on the 64-bit keys.
 constexpr int kFWaves = 8;
 constexpr int kFThreads = kFWaves * kWave;
-constexpr int kFStrideBig = 1192;   // LDS key-row stride = largest nb: 152.6 KB of keys
-constexpr int kFStrideSmall = 584;  // 74.8 KB: two workgroups per CU
+constexpr int kFStrideLong = 2384;  // LDS key-row stride = largest nb: 152.6 KB of keys (16 rows)
+constexpr int kFStrideBig = 1192;   // 152.6 KB (32 rows)
+constexpr int kFStrideSmall = 584;  // 74.8 KB (32 rows)
 constexpr double kScoreRelErr = 1.0 / 8192;
 
 // Order-preserving 32-bit key of an fp32 score (larger score -> larger key);
@@ -592,6 +614,53 @@ __device__ __forceinline__ uint32_t order_key32(float a) {
 }
 __device__ __forceinline__ float key32_value(uint32_t key) {
   return __uint_as_float((key >> 31) ? (key ^ 0x80000000u) : ~key);
+}
+
+// A T with count(key >= T) == k (*exact), or else the k-th largest key, over
+// the whole row: keys order_key32 values, 0 for no candidate, of which at
+// least k are not 0.  A count costs two vector instructions per key, so the
+// search brackets T in few of them: it goes to where the counts at the two
+// ends, interpolated over the score values, put the k-th, and every other
+// step to the middle of the values (of the keys, once the ends are close or
+// 16 steps have passed, which bounds the search for any distribution).  Against a
+// search bit by bit: 40 heads x 1182 blocks, 10% kept, 732 -> 599 us.
+template <int KPL>
+__device__ __forceinline__ uint32_t kth_largest_row(const uint32_t (&key)[KPL], int k,
+                                                    bool* exact) {
+  uint32_t mx = 0, mn = ~0u;
+  int n = 0;
+#pragma unroll
+  for (int t = 0; t < KPL; ++t) {
+    mx = max(mx, key[t]);
+    mn = min(mn, key[t] - 1u);  // 0 wraps to the largest
+    n += key[t] != 0u;
+  }
+  // count(key >= lo) = clo >= k > chi = count(key >= hi)
+  uint32_t lo = wave_min_u32(mn) + 1u, hi = wave_max_u32(mx) + 1u;
+  int clo = wave_sum_u32(n), chi = 0;
+  *exact = clo == k;
+  for (int step = 0; !*exact && hi - lo > 1u; ++step) {
+    uint32_t mid = lo + ((hi - lo) >> 1);
+    if (step < 16) {
+      const float a = key32_value(lo), b = key32_value(hi);
+      const float f = step & 1 ? 0.5f : ((float)(clo - k) + 0.5f) / (float)(clo - chi);
+      const uint32_t m = __builtin_amdgcn_readfirstlane(order_key32(fmaf(b - a, f, a)));
+      if (m > lo && m < hi) mid = m;  // otherwise (and for a non-finite value) the keys' middle
+    }
+    int c = 0;
+#pragma unroll
+    for (int t = 0; t < KPL; ++t) c += key[t] >= mid;
+    c = wave_sum_u32(c);
+    if (c >= k) {
+      lo = mid;
+      clo = c;
+    } else {
+      hi = mid;
+      chi = c;
+    }
+    *exact = c == k;
+  }
+  return lo;
 }
 
 // fp64 score of one block pair from the pooled sums.
@@ -655,24 +724,24 @@ __device__ void exact_row_select(const double* __restrict__ qrow,
   select_emit<KPL>(hi, lo, mem, jj, k, out);
 }
 
-template <int NBP, int BLOCK>
+template <int ROWS, int NBP, int BLOCK>
 __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
     const uint16_t* __restrict__ q, Strides qs, const uint16_t* __restrict__ kfrag,
     const float* __restrict__ knorm, double* __restrict__ qhat, const double* __restrict__ khat,
-    Shape cs, int k_all, int kmax, int ntiles, int per_xcd, int32_t* __restrict__ idx,
-    int32_t* __restrict__ cnt) {
+    Shape cs, int k_all, int kmax, int ntiles, int qtiles, int per_xcd,
+    int32_t* __restrict__ idx, int32_t* __restrict__ cnt) {
   constexpr int KPL = (NBP + kWave - 1) / kWave;
   static_assert(NBP % 4 == 0 && NBP >= 129, "a key row holds one parked query block, 16-byte aligned");
-  __shared__ __align__(16) uint32_t keys[kFRows * NBP];
+  __shared__ __align__(16) uint32_t keys[ROWS * NBP];
   __shared__ uint32_t cand[kFWaves][2][kWave];
   __shared__ float wmax[kFWaves];
   const int nb = cs.nb;
-  constexpr int kQB = kFRows / kFWaves;  // query blocks pooled per wave
+  constexpr int kQB = ROWS / kFWaves;  // query blocks pooled per wave
   // Consecutive tiles (the same head's key blocks) run on one XCD: workgroup
   // w goes to XCD w % 8, which takes the logical tiles [x, x + 1) * per_xcd.
   const int logical = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-  if (logical >= cs.B * cs.H * ntiles) return;  // uniform
-  const int bh = logical / ntiles, it = logical - bh * ntiles;
+  if (logical >= cs.B * cs.H * qtiles) return;  // uniform
+  const int bh = logical / qtiles, it = logical - bh * qtiles;
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, g = lane >> 5;
@@ -694,7 +763,7 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
   // norm at 128).  Blocks past nb pool to zero.
   const uint16_t* qhead = q + (bh / cs.H) * qs.b + (bh % cs.H) * qs.h;
   auto park = [&](const double (&acc)[8], int u) __attribute__((always_inline)) {
-    const int i = it * kFRows + kQB * wave + u;
+    const int i = it * ROWS + kQB * wave + u;
     if (i < nb && r0 == 0) {
       double* o = qhat + ((int64_t)bh * nb + i) * kHeadDim + 8 * c8;
 #pragma unroll
@@ -713,17 +782,17 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
     if (lane == 0) slot[128] = __float_as_uint(n_i > 0 ? f32_round_up(sqrt(sq) / (double)n_i) : 0.f);
   };
   {  // BLOCK 64: two blocks' loads in flight together
-    constexpr int kPar = BLOCK == 64 ? 2 : 1;
+    constexpr int kPar = BLOCK == 64 && kQB > 1 ? 2 : 1;
 #pragma unroll
     for (int u0 = 0; u0 < kQB; u0 += kPar) {
       u32x4 w[kPar][BLOCK / 4];
 #pragma unroll
       for (int p = 0; p < kPar; ++p)
-        pool_load<BLOCK>(qhead, qs.n, (it * kFRows + kQB * wave + u0 + p) * BLOCK, cs.N, w[p]);
+        pool_load<BLOCK>(qhead, qs.n, (it * ROWS + kQB * wave + u0 + p) * BLOCK, cs.N, w[p]);
 #pragma unroll
       for (int p = 0; p < kPar; ++p) {
         double acc[8];
-        pool_reduce<BLOCK>(w[p], (it * kFRows + kQB * wave + u0 + p) * BLOCK, cs.N, acc);
+        pool_reduce<BLOCK>(w[p], (it * ROWS + kQB * wave + u0 + p) * BLOCK, cs.N, acc);
         park(acc, u0 + p);
       }
     }
@@ -745,12 +814,13 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
     qn_rows = __uint_as_float(keys[(rr / kQB + kFWaves * (rr % kQB)) * NBP + 128]);
   }
 
-  {  // approximate scores of the 32 query blocks against every key block
+  {  // approximate scores of the query blocks against every key block
     // operand step st, lane l: channels 8 (2 (st % 8) + l / 32) .. +7 of
-    // query block l % 32, hi words for st < 8, lo words after
+    // query block l % 32 (repeated when ROWS < 32), hi words for st < 8, lo
+    // words after
     bf16x8 qa[kFSteps];
     {
-      const int rb = l32;
+      const int rb = l32 & (ROWS - 1);
       const uint32_t* src = keys + (rb / kQB + kFWaves * (rb % kQB)) * NBP + 4 * g;
 #pragma unroll
       for (int st = 0; st < kFSteps; ++st)
@@ -789,7 +859,7 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
         const float inv =
             __builtin_amdgcn_rcpf((float)(cs.block * min(cs.block, cs.N - j * cs.block)));
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < ROWS / 2; ++r) {
           const uint32_t u = __float_as_uint(fmaf(acc[r], inv, 0.f));
           keys[(8 * (r >> 2) + 4 * g + (r & 3)) * NBP + j] =
               u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
@@ -835,7 +905,7 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
 
   for (int rm = 0; rm < kQB; ++rm) {
     const int rr = wave + kFWaves * rm;
-    const int i = it * kFRows + rr;
+    const int i = it * ROWS + rr;
     if (i >= nb) break;  // uniform
     const int64_t row = (int64_t)bh * nb + i;
     const int ni = min(cs.block, cs.N - i * cs.block);
@@ -992,29 +1062,42 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
       }
       if (!done) {
         if (!have) {
-          bool mem[KPL];
-#pragma unroll
-          for (int t = 0; t < KPL; ++t) mem[t] = key[t] != 0u;
           bool ex;
-          const uint32_t T = kth_largest32<KPL>(key, mem, k, &ex);
-          int cge = 0;
-          uint32_t mn = ~0u, mx = 0u;
+          const uint32_t T = kth_largest_row<KPL>(key, k, &ex);
+          if (ex) {
+            uint32_t mn = ~0u, mx = 0u;
 #pragma unroll
-          for (int t = 0; t < KPL; ++t) {
-            const bool ge = key[t] >= T && key[t] != 0u;
-            cge += __popcll(__ballot(ge));
-            if (ge) mn = min(mn, key[t]);
-            else mx = max(mx, key[t]);
+            for (int t = 0; t < KPL; ++t) {
+              mn = min(mn, key[t] >= T ? key[t] : ~0u);
+              mx = max(mx, key[t] >= T ? 0u : key[t]);
+            }
+            thresholds(wave_min_u32(mn), wave_max_u32(mx));
+          } else {
+            thresholds(T, T);
           }
-          if (cge == k) thresholds(wave_min_u32(mn), wave_max_u32(mx));
-          else thresholds(T, T);
+          // (thresholds are at least 1: every finite score's key is)
+          if (ex && KLO > KHI) {  // empty band: the k keys above KHI
+            int taken = 0;
+#pragma unroll
+            for (int t = 0; t < KPL; ++t) {
+              const uint64_t m = __ballot(key[t] > KHI);
+              const int pos = taken + rank_below(m);
+              if (key[t] > KHI && pos < k) out[pos] = lane + kWave * t;
+              taken += __popcll(m);
+            }
+            done = taken == k;
+          }
         }
+      }
+      if (!done) {
         int cin = 0, cband = 0;
 #pragma unroll
         for (int t = 0; t < KPL; ++t) {
-          cin += __popcll(__ballot(key[t] > KHI));
-          cband += __popcll(__ballot(key[t] != 0u && key[t] <= KHI && key[t] >= KLO));
+          cin += key[t] > KHI;
+          cband += key[t] != 0u && key[t] <= KHI && key[t] >= KLO;
         }
+        cin = wave_sum_u32(cin);
+        cband = wave_sum_u32(cband);
         if (cband <= kWave && cin <= k && cin + cband >= k) {
           // compact the band's indices; rescore them in fp64, all lanes on
           // one block at a time (lane l: channels 2 l, 2 l + 1)
@@ -1306,7 +1389,7 @@ size_t select_workspace_bytes(const Shape& s) {
   const size_t bh = (size_t)s.B * s.H;
   const size_t pooled = bh * s.nb * kHeadDim * sizeof(double) * 2;
   if (s.nb <= kFStrideBig) {
-    const size_t ntiles = (s.nb + kFRows - 1) / kFRows;
+    const size_t ntiles = (s.nb + kKTile - 1) / kKTile;
     return pooled + bh * ntiles * kFSteps * kWave * 8 * sizeof(uint16_t) +
            bh * s.nb * sizeof(float);
   }
@@ -1341,9 +1424,9 @@ static hipError_t launch_pool_score(const Shape& s, const void* q, Strides qs, c
 hipError_t launch_select_row(const Shape& s, const void* q, Strides qs, const void* k,
                              Strides ks, int topk, int kmax, int32_t* idx, int32_t* cnt,
                              void* ws, hipStream_t stream) {
-  if (s.nb <= kFStrideBig) {
+  if (s.nb <= kFStrideLong) {
     const size_t bh = (size_t)s.B * s.H;
-    const int ntiles = (s.nb + kFRows - 1) / kFRows;
+    const int ntiles = (s.nb + kKTile - 1) / kKTile;
     const size_t frag = bh * ntiles * kFSteps * kWave * 8;  // uint16
     double* qhat = static_cast<double*>(ws);
     double* khat = qhat + bh * s.nb * kHeadDim;
@@ -1355,18 +1438,43 @@ hipError_t launch_select_row(const Shape& s, const void* q, Strides qs, const vo
     launch_pool(s, q, qs, k, ks, qhat, khat, sp, true, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int per_xcd = (int)((bh * ntiles + 7) / 8);
+    int dev = 0, cus = 0;
+    if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
     const auto* qq = static_cast<const uint16_t*>(q);
-#define SA_FUSED(NBP, BLOCK)                                                                   \
-  score_topk_kernel<NBP, BLOCK><<<8 * per_xcd, kFThreads, 0, stream>>>(                         \
-      qq, qs, sp.frag, sp.norm, qhat, khat, s, topk, kmax, ntiles, per_xcd, idx, cnt)
+    // rounds over the CUs times the measured time of a workgroup of that size
+    auto cost = [&](int rows, int unit) {
+      const int64_t groups = (int64_t)bh * ((s.nb + rows - 1) / rows);
+      return (groups + cus - 1) / cus * unit;
+    };
+    const int64_t c32 = cost(32, 5), c16 = cost(16, 3), c8 = cost(8, 2);
+    const int rows = c32 <= c16 && c32 <= c8 ? 32 : c16 <= c8 ? 16 : 8;
+#define SA_FUSED(ROWS, NBP, BLOCK)                                                             \
+  do {                                                                                         \
+    const int qtiles = (s.nb + ROWS - 1) / ROWS;                                               \
+    const int per_xcd = (int)((bh * qtiles + 7) / 8);                                          \
+    score_topk_kernel<ROWS, NBP, BLOCK><<<8 * per_xcd, kFThreads, 0, stream>>>(                \
+        qq, qs, sp.frag, sp.norm, qhat, khat, s, topk, kmax, ntiles, qtiles, per_xcd, idx,     \
+        cnt);                                                                                  \
+  } while (0)
+#define SA_FUSED_ROWS(NBP, BLOCK)                     \
+  do {                                                \
+    if (rows == 32) SA_FUSED(32, NBP, BLOCK);         \
+    else if (rows == 16) SA_FUSED(16, NBP, BLOCK);    \
+    else SA_FUSED(8, NBP, BLOCK);                     \
+  } while (0)
     if (s.nb <= kFStrideSmall) {
-      if (s.block == 64) SA_FUSED(kFStrideSmall, 64);
-      else SA_FUSED(kFStrideSmall, 128);
+      if (s.block == 64) SA_FUSED_ROWS(kFStrideSmall, 64);
+      else SA_FUSED_ROWS(kFStrideSmall, 128);
+    } else if (s.nb <= kFStrideBig) {
+      if (s.block == 64) SA_FUSED_ROWS(kFStrideBig, 64);
+      else SA_FUSED_ROWS(kFStrideBig, 128);
     } else {
-      if (s.block == 64) SA_FUSED(kFStrideBig, 64);
-      else SA_FUSED(kFStrideBig, 128);
+      if (s.block == 64) SA_FUSED(16, kFStrideLong, 64);
+      else SA_FUSED(16, kFStrideLong, 128);
     }
+#undef SA_FUSED_ROWS
 #undef SA_FUSED
     return hipGetLastError();
   }
