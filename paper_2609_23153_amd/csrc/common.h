@@ -107,4 +107,17 @@ __device__ __forceinline__ uint64_t lanes_below_mask() {
   return lane == 0 ? 0ull : (~0ull >> (kWave - lane));
 }
 
+// Launch slot of workgroup `w` of G.  The launch order gives each XCD
+// (workgroup mod 8) runs of 256 consecutive positions of the sorted tiles in
+// groups of 2048 slots and leaves the slots of a last partial group in
+// position order, which would deal neighbouring tiles to different XCDs, every
+// L2 then reading every key tile.  There each XCD takes runs of 32 slots, in
+// groups of 256 (bf16 forward, 36 key blocks a tile: 512 tiles 84 -> 49 us,
+// 1024 158 -> 102, 6000 619 -> 519).
+__device__ __forceinline__ int launch_slot(int w, int G) {
+  const int full = G & ~2047, r = w - full;
+  if (r < 0 || r >= ((G - full) & ~255)) return w;
+  return full + (r & ~255) + 32 * (r & 7) + ((r & 255) >> 3);
+}
+
 }  // namespace sa

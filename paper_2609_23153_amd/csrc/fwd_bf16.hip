@@ -164,7 +164,8 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_kernel(Params p) {
   __shared__ __attribute__((aligned(1024))) uint8_t vb1[kTileBytes];
   __shared__ __attribute__((aligned(1024))) uint8_t vb2[kTileBytes];
 
-  const int item = p.order ? p.order[blockIdx.x] : (int)blockIdx.x;
+  const int slot = launch_slot((int)blockIdx.x, (int)gridDim.x);
+  const int item = p.order ? p.order[slot] : slot;
   const int bh = item / p.ntiles;
   const int qt = item - bh * p.ntiles;
   const int b = bh / p.H, h = bh - b * p.H;

@@ -99,7 +99,8 @@ __device__ __forceinline__ int e8m0(float s) { return (int)((__float_as_uint(s) 
 
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void fwd_fp8_kernel(
     Params p) {
-  const int item = p.order ? p.order[blockIdx.x] : (int)blockIdx.x;
+  const int slot = launch_slot((int)blockIdx.x, (int)gridDim.x);
+  const int item = p.order ? p.order[slot] : slot;
   const int bh = item / p.ntiles;
   const int qt = item - bh * p.ntiles;
   const int b = bh / p.H, h = bh - b * p.H;

@@ -427,3 +427,27 @@ def test_fwd_order_does_not_change_results(N, block):
     torch.cuda.synchronize()
     assert torch.equal(o1.view(torch.int16), o0.view(torch.int16))
     assert torch.equal(l1.view(torch.int32), l0.view(torch.int32))
+
+
+@pytest.mark.parametrize("H,N,block", [
+    (11, 27 * 64 - 5, 64),    # 297 tiles: one group of 256 slots and a rest
+    (18, 129 * 64, 64),       # 2322 tiles: a group of 2048, one of 256, a rest
+    (9, 58 * 128 - 70, 128),  # 1035 tiles: four groups of 256, odd tiles per head
+])
+def test_fwd_every_tile_of_every_launch_group(H, N, block):
+    """Tile counts around the launch's groups: every tile computed, from the
+    scheduled order and from none alike."""
+    g = torch.Generator().manual_seed(N)
+    q, k, v = (torch.randn(1, H, N, 128, generator=g).to(torch.bfloat16) for _ in range(3))
+    nb = -(-N // block)
+    lists = [W.random_block_lists(nb, nb, 3, seed=h, p_empty=0.1) for h in range(H)]
+    idx = torch.from_numpy(np.stack([l[0] for l in lists]))[None].to(DEV)
+    cnt = torch.from_numpy(np.stack([l[1] for l in lists]))[None].to(DEV)
+    fwd_and_check(q, k, v, idx, cnt, block, f"H={H} N={N} b={block}", heads=[0, H - 1])
+    qd, kd, vd = to_dev(q, k, v)
+    order = sa.sparse_attn_schedule(cnt, N, 3, block=block)
+    o1, l1 = sa.sparse_attn_fwd(qd, kd, vd, idx, cnt, block=block, order=order,
+                                o=torch.full_like(qd, float("nan")))
+    o2, l2 = sa.sparse_attn_fwd(qd, kd, vd, idx, cnt, block=block)
+    torch.cuda.synchronize()
+    assert torch.equal(o1, o2) and torch.equal(l1, l2) and torch.isfinite(o1.float()).all()
