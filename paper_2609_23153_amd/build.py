@@ -17,8 +17,13 @@ INCLUDE = os.path.join(ROOT, "include")
 OUT_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libsparseattn.so")
 
-SOURCES = ["api.hip", "select.hip", "sched.hip", "fwd_bf16.hip", "fwd_fp8.hip", "quant_fp8.hip",
+SOURCES = ["api.hip", "select.hip", "sched.hip", "fwd_bf16.hip", "fwd_bf16_wave.hip", "fwd_fp8.hip", "quant_fp8.hip",
            "comp.hip", "linear_fp8.hip", "bwd.hip"]
+# Kernels of one wave per SIMD (512 registers): matrix products write VGPRs,
+# which the vector instructions read directly; the compiler's own choice there
+# is the other half of the register file, with a copy per element.
+VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+EXTRA = {"fwd_bf16_wave.hip": VGPR_FORM}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -42,7 +47,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
 
     def compile_one(src):
         obj = os.path.join(OUT_DIR, src.replace(".hip", ".o"))
-        out = _run([HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj])
+        out = _run([HIPCC, *FLAGS, *EXTRA.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj])
         if verbose and out.strip():
             print(out)
         return obj
@@ -86,7 +91,7 @@ def build_host_sanitized(jobs: int = 8) -> str:
 
     def compile_one(src):
         obj = os.path.join(out, src.replace(".hip", ".o"))
-        _run([HIPCC, *flags, *san, "-c", os.path.join(CSRC, src), "-o", obj])
+        _run([HIPCC, *flags, *EXTRA.get(src, []), *san, "-c", os.path.join(CSRC, src), "-o", obj])
         return obj
 
     with ThreadPoolExecutor(max_workers=jobs) as ex:

@@ -4,6 +4,9 @@
 // Eq. comp-sparse, §4.1): exact softmax attention of each 64-row query tile
 // over the union of the key blocks its query block selected.
 //
+// (fwd_bf16_wave.hip computes the same with one wave per tile, for launches
+// that give every SIMD a tile; launch_fwd_bf16 chooses.)
+//
 // One workgroup = 4 wavefronts = one 64-row query tile; two workgroups share
 // a CU.  Every selected key block is walked as 64-key tiles:
 //  * K and V tiles go straight from L2 into LDS with buffer_load ... lds (no
@@ -446,6 +449,21 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_kernel(Params p) {
 }  // namespace
 
 hipError_t launch_fwd_bf16(const Shape& s, const FwdArgs& a, hipStream_t stream) {
+  // The kernel of one wave per tile takes about 82 us a round of 4 tiles per
+  // CU (36 key blocks a tile), 58 us + 30 us x filled share for a last partial
+  // round; this one 96 us for as many tiles, in proportion.  So 58 of the
+  // partial round has to be made up for (us, this kernel / one wave: 512 tiles
+  // 49 / 66, 1024 102 / 90, 1280 123 / 145, 1800 182 / 167, 4096 354 / 329,
+  // 47,280 4200 / 3870).
+  const int grid = s.B * s.H * ((s.N + kTile - 1) / kTile);
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  const int full = grid / (4 * cus), rest = grid % (4 * cus);
+  if (rest == 0 || 14 * full + 65 * rest / (4 * cus) > 58)
+    return launch_fwd_bf16_wave(s, a, stream);
   Params p;
   p.q = static_cast<const uint16_t*>(a.q);
   p.k = static_cast<const uint16_t*>(a.k);
@@ -467,7 +485,6 @@ hipError_t launch_fwd_bf16(const Shape& s, const FwdArgs& a, hipStream_t stream)
   p.ntiles = (s.N + kTile - 1) / kTile;
   p.scale_log2 = a.softmax_scale * 1.4426950408889634f;
   p.cs = s;
-  const int grid = s.B * s.H * p.ntiles;
   fwd_bf16_kernel<<<grid, kThreads, 0, stream>>>(p);
   return hipGetLastError();
 }

@@ -78,6 +78,7 @@ struct FwdArgs {
   float softmax_scale;
 };
 hipError_t launch_fwd_bf16(const Shape& s, const FwdArgs& a, hipStream_t stream);
+hipError_t launch_fwd_bf16_wave(const Shape& s, const FwdArgs& a, hipStream_t stream);
 hipError_t launch_fwd_fp8(const Shape& s, const FwdArgs& a, hipStream_t stream);
 
 // ---- compensation branch -------------------------------------------------
