@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
+import struct
 
 import torch
 
@@ -122,9 +123,28 @@ def library() -> ctypes.CDLL:
 def _strides(t):
     if t is None:
         return (0, 0, 0)
-    if t.dim() != 4 or t.stride(3) != 1:
+    st = t.stride()
+    if len(st) != 4 or st[3] != 1:
         raise ValueError("expected a [B, H, N, d] tensor with contiguous channels")
-    return tuple(t.stride()[:3])
+    return st[:3]
+
+
+# The descriptor's fields packed at once (setting them one by one through
+# ctypes takes about 3 us, and a call of the smallest layers 10).
+_DESC = struct.Struct("@5i12qf2i4x")
+assert _DESC.size == ctypes.sizeof(SparseAttnDesc)
+
+
+def _fill_desc(*fields):
+    try:
+        return SparseAttnDesc.from_buffer_copy(_DESC.pack(*fields))
+    except (struct.error, OverflowError):  # let ctypes convert or refuse the values
+        desc = SparseAttnDesc()
+        desc.batch, desc.heads, desc.seqlen, desc.head_dim, desc.block = fields[:5]
+        for i, name in enumerate(("q_stride", "k_stride", "v_stride", "o_stride")):
+            getattr(desc, name)[:] = fields[5 + 3 * i:8 + 3 * i]
+        desc.softmax_scale, desc.causal_chunk, desc.causal_window = fields[17:]
+        return desc
 
 
 def make_desc(q, k=None, v=None, o=None, block: int = 64, softmax_scale: float = 0.0,
@@ -133,22 +153,25 @@ def make_desc(q, k=None, v=None, o=None, block: int = 64, softmax_scale: float =
     (chunk_tokens, window_chunks) restricts attention to a causal window
     (window 0: every earlier chunk); None leaves it unrestricted."""
     B, H, N, d = q.shape
-    desc = SparseAttnDesc()
-    desc.batch, desc.heads, desc.seqlen, desc.head_dim, desc.block = B, H, N, d, block
-    for field, t in (("q_stride", q), ("k_stride", k), ("v_stride", v), ("o_stride", o)):
-        getattr(desc, field)[:] = _strides(t)
-    desc.softmax_scale = softmax_scale
-    if causal is not None:
-        desc.causal_chunk, desc.causal_window = int(causal[0]), int(causal[1])
-    return desc
+    chunk, window = (0, 0) if causal is None else (int(causal[0]), int(causal[1]))
+    return _fill_desc(B, H, N, d, block, *_strides(q), *_strides(k), *_strides(v), *_strides(o),
+                      softmax_scale, chunk, window)
+
+
+def _tile_desc(cnt, seqlen, block):
+    """Descriptor of the list lengths alone (no tensor strides)."""
+    B, H, _ = cnt.shape
+    return _fill_desc(B, H, seqlen, 128, block, *(0,) * 12, 0.0, 0, 0)
 
 
 def _stream(t):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    if t.is_cuda:
+        return torch._C._cuda_getCurrentRawStream(t.device.index)
+    return torch.cuda.current_stream(t.device).cuda_stream
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _dense(t, name, dtype=torch.int32):
@@ -222,11 +245,9 @@ def sparse_attn_select(q, k, budget: int, block: int = 64, mode: int = SA_SELECT
 def sparse_attn_schedule(cnt, seqlen: int, kmax: int, block: int = 64, order=None, ws=None):
     """Launch order of the 64-row query tiles for the lists' lengths ``cnt``
     [B, H, nb].  Returns int32 [B * H * ceil(seqlen / 64)]."""
-    B, H, _ = cnt.shape
     _dense(cnt, "cnt")
     _dense(order, "order")
-    desc = SparseAttnDesc()
-    desc.batch, desc.heads, desc.seqlen, desc.head_dim, desc.block = B, H, seqlen, 128, block
+    desc = _tile_desc(cnt, seqlen, block)
     n = sparse_attn_num_tiles(desc)
     if n < 0:
         raise SparseAttnError(-2, "sparse_attn_num_tiles")
@@ -244,11 +265,9 @@ def sparse_attn_schedule_static(cnt, seqlen: int, kmax: int, order, block: int =
     """sparse_attn_schedule without a workspace (the library's per-GPU device
     array holds the counters): writes the launch order into the caller's
     ``order`` (int32 [B * H * ceil(seqlen / 64)]) and allocates nothing."""
-    B, H, _ = cnt.shape
     _dense(cnt, "cnt")
     _dense(order, "order")
-    desc = SparseAttnDesc()
-    desc.batch, desc.heads, desc.seqlen, desc.head_dim, desc.block = B, H, seqlen, 128, block
+    desc = _tile_desc(cnt, seqlen, block)
     if order.numel() != sparse_attn_num_tiles(desc):
         raise ValueError("order must hold one int32 per query tile")
     st = library().sparse_attn_schedule_static(ctypes.byref(desc), _ptr(cnt), kmax, _ptr(order),

@@ -341,3 +341,21 @@ def test_schedule_static_rejects_bad_arguments():
     over = desc(B=1, H=1023, N=1024 * 64 + 64)
     assert lib.sparse_attn_workspace_size(ctypes.byref(over), sa.SA_OP_SCHEDULE, 7) > 65536
     assert call(over, P, 7, P, None) == -2
+
+
+@pytest.mark.parametrize("kw", [
+    {}, {"block": 128, "softmax_scale": 0.3, "causal": (77, 2)}, {"softmax_scale": 1e300},
+    {"block": 2 ** 40}, {"causal": (10 ** 12, -1)}])
+def test_descriptor_fields(kw):
+    """The packed descriptor holds what setting each field through ctypes
+    gives, values beyond a field's range (converted by ctypes) included."""
+    q = torch.zeros(2, 3, 100, 128, dtype=torch.bfloat16)
+    v = torch.zeros(2, 100, 3, 128, dtype=torch.bfloat16).permute(0, 2, 1, 3)
+    ref = sa.SparseAttnDesc()
+    ref.batch, ref.heads, ref.seqlen, ref.head_dim = 2, 3, 100, 128
+    ref.block = kw.get("block", 64)
+    ref.q_stride[:] = q.stride()[:3]
+    ref.v_stride[:] = v.stride()[:3]
+    ref.softmax_scale = kw.get("softmax_scale", 0.0)
+    ref.causal_chunk, ref.causal_window = kw.get("causal", (0, 0))
+    assert bytes(sa.make_desc(q, v=v, **kw)) == bytes(ref)
