@@ -7,6 +7,7 @@ import re
 import subprocess
 
 import pytest
+import torch
 
 import paper_2609_23153_amd as sa
 
