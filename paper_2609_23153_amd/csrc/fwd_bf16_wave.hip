@@ -109,10 +109,25 @@ fwd_bf16_wave_kernel(Params p) {
   const int q0 = qt * kTile;
   const int iblk = q0 / p.block;
   const int hsh = p.block == 64 ? 1 : 2;  // log2(half tiles per block)
-  const list_ptr list = (list_ptr)(p.idx + ((int64_t)bh * p.nb + iblk) * p.kmax);
-  const int total = min(max(p.cnt[(int64_t)bh * p.nb + iblk], 0), p.kmax) << hsh;
   const int lane = threadIdx.x & (kWave - 1);
   const int g = lane >> 5, l32 = lane & 31;
+  // (the loads that the first step waits for are issued together: Q, the list
+  // length and the first entries)
+  // Q fragments (B operand of K Q^T): row 32 qh + l32, channels 16 ks + 8 g ..
+  // +7 (rows past the end repeat the last one; they are not stored)
+  bf16x8 qf[2][8];
+#pragma unroll
+  for (int qh = 0; qh < 2; ++qh) {
+    const uint16_t* qp = p.q + b * p.qs.b + h * p.qs.h +
+                         (int64_t)min(q0 + 32 * qh + l32, p.N - 1) * p.qs.n + 8 * g;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qf[qh][ks] = as_bf16x8(ld16(qp + 16 * ks));
+  }
+  const list_ptr list = (list_ptr)(p.idx + ((int64_t)bh * p.nb + iblk) * p.kmax);
+  int ahead[4];  // the entries of half tiles 0..3
+#pragma unroll
+  for (int n = 0; n < 4; ++n) ahead[n] = list[min(n >> hsh, p.kmax - 1)];
+  const int total = min(max(p.cnt[(int64_t)bh * p.nb + iblk], 0), p.kmax) << hsh;
 
   // Allowed keys [key_lo, key_hi) of this lane's query of each half; a half
   // tile needs the per-score mask unless it lies inside every row's range:
@@ -142,8 +157,30 @@ fwd_bf16_wave_kernel(Params p) {
     }
     return p.N;
   };
-  // starts of the current half tile and the three after it
-  int s0 = take(), s1 = take(), s2 = take(), s3 = take();
+  // starts of the current half tile and the three after it: from the entries
+  // read together if they are all valid, else one by one
+  int s0, s1, s2, s3;
+  {
+    int st[4];
+    bool valid = total >= 4;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      st[n] = ahead[n] * p.block + (n & ((1 << hsh) - 1)) * kHalf;
+      valid = valid && ahead[n] >= 0 && ahead[n] < p.nb && st[n] < p.N;
+    }
+    if (valid) {
+      s0 = st[0];
+      s1 = st[1];
+      s2 = st[2];
+      s3 = st[3];
+      pos = 3;
+    } else {
+      s0 = take();
+      s1 = take();
+      s2 = take();
+      s3 = take();
+    }
+  }
 
   // Copies: instruction i moves rows 4 i .. 4 i + 3 of a half tile, lane l the
   // 16 bytes that the swizzle places in slot l % 16 of row 4 i + l / 16.
@@ -205,17 +242,6 @@ fwd_bf16_wave_kernel(Params p) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) copy_v(0, i, s0);
 
-  // Q fragments (B operand of K Q^T): row 32 qh + l32, channels 16 ks + 8 g ..
-  // +7 (rows past the end repeat the last one; they are not stored)
-  bf16x8 qf[2][8];
-#pragma unroll
-  for (int qh = 0; qh < 2; ++qh) {
-    const uint16_t* qp = p.q + b * p.qs.b + h * p.qs.h +
-                         (int64_t)min(q0 + 32 * qh + l32, p.N - 1) * p.qs.n + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) qf[qh][ks] = as_bf16x8(ld16(qp + 16 * ks));
-  }
-
   f32x16 acc[2][4], s[2];
   bf16x8 kf[8], vf[8];  // vf[2 dt + cs]
   u32x4 pw[2][2];       // P^T of a query half, k-step cs
@@ -234,7 +260,7 @@ fwd_bf16_wave_kernel(Params p) {
   const float c = p.scale_log2;
   // Keys outside the window of a lane's query (or past N): score -inf.
   auto mask = [&](int st, int qh) __attribute__((always_inline)) {
-    if (st + kHalf > tile_hi || st < tile_lo) {  // wave-uniform
+    if (__builtin_expect(st + kHalf > tile_hi || st < tile_lo, 0)) {  // wave-uniform
       const int hi = key_hi[qh] - st - 4 * g, lo = key_lo[qh] - st - 4 * g;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -271,7 +297,7 @@ fwd_bf16_wave_kernel(Params p) {
     pw[qh][1][3] = cvt_pk(e[14], e[15]);
     // with m2 = -inf every probability is +inf or NaN, so the first half tile
     // always takes the branch
-    if (__any(!(ts <= kSumCap))) {  // wave-uniform: raise the reference max
+    if (__builtin_expect(__any(!(ts <= kSumCap)), 0)) {  // wave-uniform: raise the reference max
       float mx = s[qh][0];
 #pragma unroll
       for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[qh][r]);
@@ -373,7 +399,7 @@ fwd_bf16_wave_kernel(Params p) {
     if (pos + 1 < total) {
       const int j = __builtin_amdgcn_readfirstlane(raw);
       const int st = j * p.block + ((pos + 1) & ((1 << hsh) - 1)) * kHalf;
-      if (j >= 0 && j < p.nb && st < p.N) {
+      if (__builtin_expect(j >= 0 && j < p.nb && st < p.N, 1)) {
         ++pos;
         s3 = st;
       } else {
