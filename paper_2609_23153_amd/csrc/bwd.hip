@@ -7,10 +7,11 @@
 //   dQ_i = tau dS K_U,  dK_U += tau dS^T Q_i,  D_i = rowsum(dO_i o O_i).
 //
 // Kernels:
-//  * bwd_dot_kernel: D = rowsum(dO o O) in fp32, one 16-lane group per token;
-//  * bwd_bits_clear / bwd_bits_set: the transposed selection as a bitmap,
-//    bit i of row j set when query block i selected key block j (atomic OR,
-//    order independent, so the result is deterministic);
+//  * bwd_dot_kernel: D = rowsum(dO o O) in fp32, one 16-lane group per token,
+//    and the bitmap cleared;
+//  * bwd_bits_set: the transposed selection as a bitmap, bit i of row j set
+//    when query block i selected key block j (atomic OR, order independent, so
+//    the result is deterministic);
 //  * bwd_dq_kernel: one workgroup per 64-row query tile walks its list like
 //    the forward (wave (rh, kh): query rows 32 rh.., keys 32 kh.. of a tile):
 //      S^T = K Q^T, dP^T = V dO^T (8 + 8 MFMAs), P and dS per lane,
@@ -50,13 +51,23 @@ __device__ __forceinline__ uint32_t cvt_bf16x2(float lo, float hi) {
 }
 
 // Work item of workgroup `slot` among G: each XCD (slot % 8) walks runs of
-// 64 consecutive items, so tiles whose operands overlap share that XCD's L2;
-// the slots of the last partial group keep their own item.
+// consecutive items, so tiles whose operands overlap share that XCD's L2: runs
+// of 64, then of 32 and 8 in what is left of a group of 512 and of 256 (where
+// neighbours used to be dealt to 8 XCDs: 28 heads x 1006 tokens 47.5 -> 44.4 us,
+// 2 x 20,000 270 -> 256); the slots of the last partial group of 64 keep their
+// own item.
 __device__ __forceinline__ int xcd_item(int slot, int G) {
-  constexpr int kRunB = 64, kGroup = 8 * kRunB;
-  if (slot >= (G / kGroup) * kGroup) return slot;
-  const int r = slot >> 3;
-  return (r / kRunB) * kGroup + (slot & 7) * kRunB + r % kRunB;
+  int base = 0;
+#pragma unroll
+  for (int run : {64, 32, 8}) {
+    const int group = 8 * run, full = base + (G - base) / group * group;
+    if (slot < full) {
+      const int s = slot - base, r = s >> 3;
+      return base + (r / run) * group + (s & 7) * run + r % run;
+    }
+    base = full;
+  }
+  return slot;
 }
 
 // 16-byte chunk c of tile row r sits at slot c ^ h(r), h(r) = 4 (r % 4) +
@@ -107,11 +118,15 @@ struct BwdParams {
   Shape cs;  // causal window (chunk 0: none) and N
 };
 
-// ---- D = rowsum(dO o O) -------------------------------------------------
+// ---- D = rowsum(dO o O), and the cleared bitmap ----------------------------
+// (a head has 16 N threads here and at most 2 N words of the bitmap: clearing
+// it in a launch of its own took 4 to 5 us)
 __global__ __launch_bounds__(kThreads) void bwd_dot_kernel(BwdParams p) {
   const int64_t tok = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);  // token of this head
   const int c = threadIdx.x & 15;
   const int bh = blockIdx.y;
+  const int64_t words = (int64_t)p.nb * p.nw, word = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (word < words) p.bits[bh * words + word] = 0u;
   if (tok >= p.N) return;
   const int b = bh / p.H, h = bh - b * p.H;
   const int64_t base = b * p.os.b + h * p.os.h + tok * p.os.n + 8 * c;
@@ -128,11 +143,6 @@ __global__ __launch_bounds__(kThreads) void bwd_dot_kernel(BwdParams p) {
 }
 
 // ---- transposed selection bitmap ----------------------------------------
-__global__ __launch_bounds__(kThreads) void bwd_bits_clear_kernel(uint32_t* bits, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i < n) bits[i] = 0u;
-}
-
 __global__ __launch_bounds__(kThreads) void bwd_bits_set_kernel(BwdParams p) {
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6);  // query block of head blockIdx.y
   const int bh = blockIdx.y;
@@ -742,10 +752,7 @@ hipError_t launch_bwd(const Shape& s, const BwdIn& in, void* ws, hipStream_t str
   const size_t dbytes = ((size_t)s.B * s.H * s.N * sizeof(float) + 255) / 256 * 256;
   p.bits = reinterpret_cast<uint32_t*>(w + dbytes);
   const int bh = s.B * s.H;
-  const int64_t nbits = (int64_t)bh * s.nb * p.nw;
   bwd_dot_kernel<<<dim3((unsigned)((s.N + 15) / 16), (unsigned)bh), kThreads, 0, stream>>>(p);
-  bwd_bits_clear_kernel<<<(unsigned)((nbits + kThreads - 1) / kThreads), kThreads, 0, stream>>>(
-      p.bits, nbits);
   bwd_bits_set_kernel<<<dim3((unsigned)((s.nb + 3) / 4), (unsigned)bh), kThreads, 0, stream>>>(p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

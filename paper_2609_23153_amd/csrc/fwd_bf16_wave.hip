@@ -67,14 +67,6 @@ __device__ __forceinline__ void wait_vm16() {
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(0x4F70);
 }
-__device__ __forceinline__ void wait_vm12() {
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0x0F7C);
-}
-__device__ __forceinline__ void wait_lgkm12() {
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0xCC7F);
-}
 __device__ __forceinline__ void wait_lgkm0() {
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(0xC07F);
