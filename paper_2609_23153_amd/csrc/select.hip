@@ -1170,15 +1170,17 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
 //   top1   : each row's best key block (excluded from the global ranking)
 //   radix  : the (budget - nqb)-th largest order key T among the remaining
 //            pairs, by 8 passes of 8 bits (a 256-bin histogram, then one
-//            workgroup per head picks the digit), and the number r of pairs
-//            equal to T that are kept (those first in (i, j) order)
+//            workgroup per head picks the digit; the passes after a bin that
+//            is kept whole do nothing), and the number r of pairs equal to T
+//            that are kept (those first in (i, j) order)
 //   counts : per row, remaining pairs with key > T and with key == T
 //   row k  : c_i = 1 + above_i + clamp(r - (ties in rows < i), 0, ties_i)
 struct HeadState {
   unsigned long long prefix;  // radix prefix; T after the last pass
   long long need;             // rank still to find among the keys == prefix
   int none;                   // no pair beyond the row bests is kept
-  int pad[3];
+  int done;                   // every key that matches the prefix is kept: no more digits
+  int pad[2];
 };
 constexpr int kBins = 256;
 
@@ -1197,6 +1199,7 @@ __global__ __launch_bounds__(kBins) void head_init_kernel(HeadWs w, long long re
     w.st[bh].prefix = 0ull;
     w.st[bh].need = rest;
     w.st[bh].none = rest == 0;
+    w.st[bh].done = 0;
   }
 }
 
@@ -1230,12 +1233,17 @@ __global__ __launch_bounds__(256) void row_top1_kernel(const double* __restrict_
 
 // Histogram of the next 8-bit digit (bits shift..shift+7) of the order keys
 // of the remaining pairs that match the prefix found so far.  Blocks of 4
-// rows; equal digits of a wave are counted with one ballot and one LDS add.
+// rows, one LDS add per pair: finding equal digits with ballots to add them at
+// once takes longer, except where a whole wave has one digit, and there it is
+// equal (the selection of 12 heads x 512 x 512: 182 -> 137 us together with the
+// passes left out, 5 x 1744 x 1744: 694 -> 489, all scores equal: 69 -> 69;
+// picking the digit in the pass's last workgroup instead of a launch needs
+// fences that cost more, 466).
 __global__ __launch_bounds__(256) void head_hist_kernel(const double* __restrict__ scores, int nb,
                                                         HeadWs w, int shift) {
   __shared__ uint32_t h[kBins];
   const int bh = blockIdx.y;
-  if (w.st[bh].none) return;  // uniform per workgroup
+  if (w.st[bh].none || w.st[bh].done) return;  // uniform per workgroup
   const uint64_t prefix = w.st[bh].prefix;
   const uint64_t mask = shift == 56 ? 0ull : ~0ull << (shift + 8);
   h[threadIdx.x] = 0u;
@@ -1246,24 +1254,10 @@ __global__ __launch_bounds__(256) void head_hist_kernel(const double* __restrict
     const int64_t row = (int64_t)bh * nb + i;
     const double* s = scores + row * nb;
     const int skip = w.top1[row];
-    for (int j0 = 0; j0 < nb; j0 += kWave) {
-      const int j = j0 + lane;
-      bool act = false;
-      uint32_t bin = 0;
-      if (j < nb && j != skip) {
-        const uint64_t key = order_key(s[j]);
-        act = (key & mask) == (prefix & mask);
-        bin = (uint32_t)(key >> shift) & (kBins - 1);
-      }
-      uint64_t left = __ballot(act);
-      while (left) {
-        const int first = __ffsll((long long)left) - 1;
-        const uint32_t b = __shfl(bin, first, kWave);
-        const uint64_t same = __ballot(act && bin == b);
-        if (lane == first) atomicAdd(&h[b], (uint32_t)__popcll(same));
-        left &= ~same;
-        if (act && bin == b) act = false;
-      }
+    for (int j = lane; j < nb; j += kWave) {
+      const uint64_t key = order_key(s[j]);
+      if (j != skip && (key & mask) == (prefix & mask))
+        atomicAdd(&h[(uint32_t)(key >> shift) & (kBins - 1)], 1u);
     }
   }
   __syncthreads();
@@ -1279,7 +1273,7 @@ __global__ __launch_bounds__(kBins) void head_radix_step_kernel(HeadWs w, int sh
   const int d = kBins - 1 - t;  // thread t holds bin d: t ascending = digit descending
   const uint32_t c = w.hist[bh * kBins + d];
   w.hist[bh * kBins + d] = 0u;
-  if (w.st[bh].none) return;  // uniform per workgroup
+  if (w.st[bh].none || w.st[bh].done) return;  // uniform per workgroup
   uint32_t incl = c;
 #pragma unroll
   for (int o = 1; o < kWave; o <<= 1) {
@@ -1293,8 +1287,12 @@ __global__ __launch_bounds__(kBins) void head_radix_step_kernel(HeadWs w, int sh
   const long long excl = (long long)incl - c;  // keys in higher digits
   __syncthreads();
   if (c > 0 && excl < need && (long long)incl >= need) {
+    // when all keys of the bin are kept, the prefix with zeros below is the
+    // threshold: they are all above or equal to it, and need covers the equal
+    // ones (of 12 heads x 512 x 512 scores the bin holds one key after 4 digits)
     w.st[bh].prefix |= (unsigned long long)d << shift;
     w.st[bh].need = need - excl;
+    w.st[bh].done = need - excl == (long long)c;
   }
 }
 
