@@ -100,7 +100,7 @@ struct StateArgs {
   float* partial;  // [BH][nc * nsub][kStateElems], lane-register order
   Strides kns, vs;
   int H, N;
-  int span;  // tokens per causal chunk (N without a window)
+  int span;   // tokens per causal chunk (N without a window)
   int nc;    // causal chunks, ceil(N / span)
   int nsub;  // 1024-token sub-chunks per causal chunk, ceil(span / 1024)
 };
@@ -355,8 +355,9 @@ struct OutArgs {
   uint16_t* o;
   Strides qns, gs, oss;
   int H, N;
-  int span;  // tokens per causal chunk (N without a window)
-  int ntg;   // workgroups per causal chunk, ceil(span / (kOutTiles * 128))
+  int span;   // tokens per causal chunk (N without a window)
+  int tiles;  // tiles of 128 tokens per workgroup
+  int ntg;    // workgroups per causal chunk, ceil(span / (tiles * 128))
   float eps;
 };
 
@@ -392,7 +393,7 @@ __device__ __forceinline__ void load_tok(const OutArgs& a, int b, int h, int tok
   gv = a.gate[b * a.gs.b + h * a.gs.h + (int64_t)tokc * a.gs.n];
 }
 
-// One workgroup per (head, kOutTiles tiles of 128 tokens): C^T (as bf16 hi +
+// One workgroup per (head, up to kOutTiles tiles of 128 tokens): C^T (as bf16 hi +
 // lo) and P_q are staged into LDS once, then the tiles stream through, the
 // next tile's per-token loads issued before the current tile is computed.
 constexpr int kOutTiles = 8;
@@ -409,8 +410,8 @@ __global__ __launch_bounds__(256, 2) void comp_out_kernel(OutArgs a) {
   // all of them using that chunk's state, in tiles of 128
   const int cc = blockIdx.y / a.ntg, grp = blockIdx.y - cc * a.ntg;
   const int c_end = min((cc + 1) * a.span, a.N);
-  const int t_beg = cc * a.span + grp * kOutTiles * kSub;
-  const int t_end = min(t_beg + kOutTiles * kSub, c_end);
+  const int t_beg = cc * a.span + grp * a.tiles * kSub;
+  const int t_end = min(t_beg + a.tiles * kSub, c_end);
   if (t_beg >= t_end) return;  // uniform: a short last chunk
   const int ntile = (t_end - t_beg + kSub - 1) / kSub;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
@@ -638,6 +639,28 @@ hipError_t launch_comp_state(const Shape& s, const CompStateIn& in, float* state
   return hipGetLastError();
 }
 
+// Tiles of 128 tokens per comp_out workgroup, 1 to kOutTiles: those for which
+// the most loaded CU does the least, where staging C^T and P_q costs 7 units and
+// a tile 5 (one workgroup of 1, 2, 4, 8 tiles a CU takes 9.5, 14.2, 22.7, 37.6
+// us).  Always 8 -> by the rule, us: 2 heads x 4096 tokens 39 -> 10 (1 tile), 40
+// x 8000 71 -> 60 (3), 12 x 32760 92 -> 79 (4), 40 x 20000 165 -> 153 (5), 40 x
+// 75600 stays at 8 (551); 16 or 32 tiles gain 1% there and lose elsewhere.
+static int out_tiles(const Shape& s, int cus) {
+  const int64_t groups = (int64_t)s.B * s.H * comp_state_chunks(s);
+  const int sub = (comp_span(s) + kSub - 1) / kSub;  // tiles of a causal chunk
+  int64_t best = 0;
+  int tiles = kOutTiles;
+  for (int t = kOutTiles; t >= 1; --t) {
+    const int64_t rounds = (groups * ((sub + t - 1) / t) + cus - 1) / cus;
+    const int64_t cost = rounds * (7 + 5 * t);
+    if (t == kOutTiles || cost < best) {
+      best = cost;
+      tiles = t;
+    }
+  }
+  return tiles;
+}
+
 hipError_t launch_comp_out(const Shape& s, const CompOutIn& in, hipStream_t stream) {
   OutArgs a;
   a.qn = static_cast<const uint16_t*>(in.q_norm);
@@ -655,7 +678,13 @@ hipError_t launch_comp_out(const Shape& s, const CompOutIn& in, hipStream_t stre
   a.N = s.N;
   a.eps = in.eps;
   a.span = comp_span(s);
-  a.ntg = (a.span + kOutTiles * kSub - 1) / (kOutTiles * kSub);
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess)
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  a.tiles = out_tiles(s, cus);
+  a.ntg = (a.span + a.tiles * kSub - 1) / (a.tiles * kSub);
   comp_out_kernel<<<dim3(s.B * s.H, comp_state_chunks(s) * a.ntg), 256, 0, stream>>>(a);
   return hipGetLastError();
 }

@@ -184,3 +184,34 @@ def test_comp_causal_full_size_heads():
     for h in range(2):
         check_head_causal(0, h, qn, kn, v, o_s, pq, pk, gamma, gate, rope, state, o, causal,
                           "14B-720P causal")
+
+
+@pytest.mark.parametrize("heads,n", [(1, 130), (2, 4096), (6, 8200), (40, 8000), (12, 32760),
+                                     (40, 20000), (3, 111600), (20, 12345)])
+@pytest.mark.parametrize("chunk", [0, 3000])
+def test_comp_out_tiles_per_workgroup(heads, n, chunk):
+    """A workgroup takes 1 to 8 tiles of tokens, by the number of workgroups
+    that makes (1, 1, 2, 3, 4, 5, 6, 8 at 256 CUs without chunks).  A token's
+    output depends on its own inputs and the state alone, so pieces computed
+    by themselves, with one tile each, give the same bytes."""
+    g = torch.Generator(device=DEV).manual_seed(heads + n)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV)
+    q, o_s = rnd(1, heads, n, 128).bfloat16(), rnd(1, heads, n, 128).bfloat16()
+    pq = (rnd(heads, R, 128) / 11).bfloat16()
+    rope = rnd(n, R // 2, 2)
+    gate = rnd(1, heads, n)
+    causal = (chunk, 0) if 0 < chunk < n else None
+    nc = -(-n // chunk) if causal else 1
+    states = rnd(1, heads, nc, 128, R)
+    o = sa.sparse_attn_comp_out(q, pq, rope, states if causal else states[:, :, 0].contiguous(),
+                                gate, o_s, causal=causal)
+    span = chunk if causal else n
+    for c in sorted({0, nc // 2, nc - 1}):
+        beg, end = c * span, min(n, (c + 1) * span)
+        for a, b in {(beg, min(end, beg + 129)), ((beg + end) // 2, min(end, (beg + end) // 2 + 300)),
+                     (max(beg, end - 257), end)}:
+            cut = lambda t: t[:, :, a:b].contiguous()
+            part = sa.sparse_attn_comp_out(cut(q), pq, rope[a:b].contiguous(),
+                                           states[:, :, c].contiguous(), cut(gate), cut(o_s))
+            assert torch.equal(part.view(torch.int16), cut(o).view(torch.int16)), (c, a, b)
+    say(f"  comp out {heads}x{n}, chunk {chunk}: pieces equal")
