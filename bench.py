@@ -40,7 +40,7 @@ TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "hbm_traffic_wan14b_720p.txt")
 # sources each kernel's counters depend on (sched.hip: the launch order;
 # quant_fp8.hip: the fp8 operand layout)
 TRAFFIC_SOURCES = {
-    "fwd_bf16_kernel": ("fwd_bf16.hip", "common.h", "launch.h", "sched.hip"),
+    "fwd_bf16_wave_kernel": ("fwd_bf16_wave.hip", "fwd_bf16.hip", "common.h", "launch.h", "sched.hip"),
     "fwd_fp8_kernel": ("fwd_fp8.hip", "quant_fp8.hip", "common.h", "launch.h", "sched.hip"),
     "pool_kernel": ("select.hip", "common.h", "launch.h"),
     "score_topk_kernel": ("select.hip", "common.h", "launch.h"),
@@ -316,7 +316,7 @@ def bench_causal(args, sa, W, dev, wl, q, k, v):
                         "fwd": round(ms[2], 4)},
         "ms_per_step": round(sum(ms), 4),
         "mean_kept_blocks": round(float(cnt.float().mean().item()), 2),
-        "roofline": {"kernel": "fwd_bf16_kernel", "bound": "mfma", "achieved": round(tf, 2),
+        "roofline": {"kernel": "fwd_bf16_wave_kernel", "bound": "mfma", "achieved": round(tf, 2),
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(tf / PEAK_BF16_TFLOPS, 4), "traffic": None,
                      "flops_per_launch": flops,
@@ -410,7 +410,7 @@ def bench_path(args, sa, W, dev, name):
         "ms_per_call_cold": {n: med(cold[n]) for n, _ in phases},
         "ms_per_step": round(step_ms, 4),
         "dense_equiv_tflops_step": round(dense / (step_ms * 1e-3) / 1e12, 2),
-        "roofline": {"kernel": "fwd_bf16_kernel", "bound": "mfma", "achieved": round(tf, 2),
+        "roofline": {"kernel": "fwd_bf16_wave_kernel", "bound": "mfma", "achieved": round(tf, 2),
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(tf / PEAK_BF16_TFLOPS, 4), "traffic": None,
                      "flops_per_launch": flops},
@@ -742,10 +742,10 @@ def main():
             "note": "Q and K read once, lists written; the whole selection call"},
         "timing": timing,
         "roofline": {
-            "kernel": "fwd_bf16_kernel", "bound": "mfma",
+            "kernel": "fwd_bf16_wave_kernel", "bound": "mfma",
             "achieved": round(fwd_tflops, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": round(fwd_tflops / PEAK_BF16_TFLOPS, 4),
-            "traffic": measured_traffic("fwd_bf16_kernel", wl.name),
+            "traffic": measured_traffic("fwd_bf16_wave_kernel", wl.name),
             "flops_per_launch": flops,
             "algorithmic_bytes_per_launch": 4 * B * H * N * d * 2 + B * H * N * 4
                                             + B * H * nb * (k + 1) * 4,

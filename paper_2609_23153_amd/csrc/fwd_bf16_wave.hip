@@ -23,7 +23,7 @@
 //    registers, the row sum is 16 plain adds (v_dot2 takes 13 cycles when it
 //    follows an MFMA), the reference max is raised lazily.
 // Measured at 40 heads x 75,600 tokens, 36 of 1182 blocks of 64 (3.57 TFLOP):
-// 3.87 ms, where the four-wave kernel takes 4.15 to 4.4 on the same box; its
+// 3.84 ms, where the four-wave kernel takes 4.15 to 4.4 on the same box; its
 // products alone take 2.63 ms (the rate of a large bf16 GEMM on this card, 1.3
 // PFLOP/s), its copies alone 2.63 and all but the copies 3.02.
 #include "common.h"

@@ -15,9 +15,10 @@
 // all tiles itself (the list lengths come from L2, a few 8-bit counters per
 // thread), which takes less time than two further launches: 47,280 tiles 4.8
 // us (22 in three launches), 128 tiles 2.9 us (15).  Its work grows with the
-// square of the tiles, hence the limit.  Beyond, three launches: class counts per chunk, one exclusive
-// scan of the counts (classes descending, chunks ascending), and a scatter
-// that writes every tile straight into its launch slot.
+// square of the tiles, hence the limit.  Beyond, three launches: class counts
+// per chunk, one exclusive scan of the counts (classes descending, chunks
+// ascending), and a scatter that writes every tile straight into its launch
+// slot.
 #include <mutex>
 
 #include "common.h"
