@@ -107,6 +107,30 @@ __device__ __forceinline__ uint64_t lanes_below_mask() {
   return lane == 0 ? 0ull : (~0ull >> (kWave - lane));
 }
 
+// The softmax states of the even and the odd 32-key half tiles of a query,
+// (m, l) and (m_o, l_o), put together: weights of the two accumulators, and the
+// log-sum-exp.  Both bf16 forward kernels keep these two states and merge them
+// here, each operation written out, so that they give the same bytes.
+struct KeyHalves {
+  float m, l, c0, c1;
+  __device__ __forceinline__ float merge(float a, float a_o) const { return fmaf(a, c0, a_o * c1); }
+  __device__ __forceinline__ float lse() const {
+    return l > 0.f ? (m + __builtin_amdgcn_logf(l)) * 0.69314718055994531f : -INFINITY;
+  }
+};
+__device__ __forceinline__ KeyHalves merge_key_halves(float m, float l, float m_o, float l_o) {
+  KeyHalves k;
+  k.m = fmaxf(m, m_o);
+  const float ms = k.m == -INFINITY ? 0.f : k.m;
+  const float a0 = __builtin_amdgcn_exp2f(m - ms);
+  const float a1 = __builtin_amdgcn_exp2f(m_o - ms);
+  k.l = fmaf(l, a0, l_o * a1);
+  const float inv = k.l > 0.f ? 1.f / k.l : 0.f;
+  k.c0 = a0 * inv;
+  k.c1 = a1 * inv;
+  return k;
+}
+
 // Launch slot of workgroup `w` of G.  The launch order gives each XCD
 // (workgroup mod 8) runs of 256 consecutive positions of the sorted tiles in
 // groups of 2048 slots and leaves the slots of a last partial group in

@@ -4,8 +4,8 @@
 // Eq. comp-sparse, §4.1): exact softmax attention of each 64-row query tile
 // over the union of the key blocks its query block selected.
 //
-// (fwd_bf16_wave.hip computes the same with one wave per tile, for launches
-// that give every SIMD a tile; launch_fwd_bf16 chooses.)
+// (fwd_bf16_wave.hip computes the same bytes with one wave per tile, for
+// launches that give every SIMD a tile; launch_fwd_bf16 chooses.)
 //
 // One workgroup = 4 wavefronts = one 64-row query tile; two workgroups share
 // a CU.  Every selected key block is walked as 64-key tiles:
@@ -415,13 +415,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_kernel(Params p) {
   if (kh == 0) {
     const float m_o = mls[lane];
     const float l_o = mls[kWave + lane];
-    const float mm = fmaxf(m2, m_o);
-    const float ms = mm == -INFINITY ? 0.f : mm;
-    const float a0 = __builtin_amdgcn_exp2f(m2 - ms);
-    const float a1 = __builtin_amdgcn_exp2f(m_o - ms);
-    const float l = lsum * a0 + l_o * a1;
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-    const float c0 = a0 * inv, c1 = a1 * inv;
+    const KeyHalves m = merge_key_halves(m2, lsum, m_o, l_o);
     const int row = q0 + rh * 32 + l32;
     if (row < p.N) {
       uint16_t* op = p.o + b * p.os.b + h * p.os.h + (int64_t)row * p.os.n;
@@ -432,16 +426,14 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_kernel(Params p) {
           float x[4];
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            x[r] = acc[dt][4 * j + r] * c0 + mrg[(dt * 16 + 4 * j + r) * kWave + lane] * c1;
+            x[r] = m.merge(acc[dt][4 * j + r], mrg[(dt * 16 + 4 * j + r) * kWave + lane]);
           u32x2 w;
           w[0] = pack_bf16x2(x[0], x[1]);
           w[1] = pack_bf16x2(x[2], x[3]);
           *reinterpret_cast<u32x2*>(op + dt * 32 + 8 * j + 4 * g) = w;
         }
       }
-      if (p.lse && g == 0)
-        p.lse[(int64_t)bh * p.N + row] =
-            l > 0.f ? (mm + __builtin_amdgcn_logf(l)) * 0.69314718055994531f : -INFINITY;
+      if (p.lse && g == 0) p.lse[(int64_t)bh * p.N + row] = m.lse();
     }
   }
 }

@@ -2,9 +2,9 @@
 compensation kernel that instruction gave wrong sums when its accumulators
 were registers an in-flight MFMA was reading; the forward is safe as long as
 no v_dot2c accumulator is ever an MFMA operand.  This test compiles the
-forward for gfx950 (device assembly, the library's own flags) and checks that
-property on the code the compiler produces, so a compiler change that
-allocates differently fails here instead of giving wrong sums."""
+two forward kernels for gfx950 (device assembly, the library's own flags) and
+checks that property on the code the compiler produces, so a compiler change
+that allocates differently fails here instead of giving wrong sums."""
 import os
 import re
 import shutil
@@ -14,7 +14,8 @@ import pytest
 
 from paper_2609_23153_amd import build as B
 
-KERNEL = "_ZN2sa12_GLOBAL__N_115fwd_bf16_kernelENS0_6ParamsE"
+KERNELS = [("fwd_bf16.hip", "_ZN2sa12_GLOBAL__N_115fwd_bf16_kernelENS0_6ParamsE"),
+           ("fwd_bf16_wave.hip", "_ZN2sa12_GLOBAL__N_120fwd_bf16_wave_kernelENS0_6ParamsE")]
 
 
 def _regs(tok):
@@ -64,13 +65,14 @@ def test_scanner_sees_an_overlap():
 
 @pytest.mark.skipif(not os.path.exists(B.HIPCC) and shutil.which("hipcc") is None,
                     reason="hipcc not available")
-def test_fwd_bf16_dot2c_accumulators_are_never_mfma_operands(tmp_path):
-    out = tmp_path / "fwd_bf16.s"
-    cmd = [B.HIPCC, *B.FLAGS, "--cuda-device-only", "-S",
-           os.path.join(B.CSRC, "fwd_bf16.hip"), "-o", str(out)]
+@pytest.mark.parametrize("src,kernel", KERNELS)
+def test_fwd_bf16_dot2c_accumulators_are_never_mfma_operands(tmp_path, src, kernel):
+    out = tmp_path / "k.s"
+    cmd = [B.HIPCC, *B.FLAGS, *B.EXTRA.get(src, []), "--cuda-device-only", "-S",
+           os.path.join(B.CSRC, src), "-o", str(out)]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
-    instrs = kernel_instructions(out.read_text(), KERNEL)
+    instrs = kernel_instructions(out.read_text(), kernel)
     n, bad = dot2c_mfma_overlap(instrs)
     assert n > 0, "the forward no longer uses v_dot2c: drop this test"
     assert not bad, f"v_dot2c accumulators also used as MFMA operands: {sorted(bad)}"
