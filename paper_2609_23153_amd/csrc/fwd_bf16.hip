@@ -441,12 +441,19 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_kernel(Params p) {
 }  // namespace
 
 hipError_t launch_fwd_bf16(const Shape& s, const FwdArgs& a, hipStream_t stream) {
-  // The kernel of one wave per tile takes about 82 us a round of 4 tiles per
-  // CU (36 key blocks a tile), 58 us + 30 us x filled share for a last partial
-  // round; this one 96 us for as many tiles, in proportion.  So 58 of the
-  // partial round has to be made up for (us, this kernel / one wave: 512 tiles
-  // 49 / 66, 1024 102 / 90, 1280 123 / 145, 1800 182 / 167, 4096 354 / 329,
-  // 47,280 4200 / 3870).
+  // Both kernels give the same bytes.  The one of one wave per tile takes about
+  // 85 us a round of 4 tiles per CU (36 key blocks a tile), 58 us + 30 us x
+  // filled share for a last partial round; this one 96 us for as many tiles, in
+  // proportion.  So 58 of the partial round has to be made up for (us, this
+  // kernel / one wave: 512 tiles 49 / 66, 1024 105 / 97, 1280 123 / 145, 1800
+  // 182 / 167, 4096 354 / 329, 47,280 4200 / 4000).
+  // A single list takes it twice as long, 1.44 us a block against 0.69, so it
+  // loses where some lists are much longer than the mean, and it is left to
+  // lists that a kmax below the row of key blocks keeps alike (a row top-k).
+  // With kmax = nb (a whole-head budget) the longest may be the whole row: 12
+  // heads x 512 blocks, 36 kept a row but all of one: 637 / 872 us, 2 heads 354 /
+  // 737; lengths spread exponentially 1027 / 1170, 2 heads 197 / 371; at a
+  // spread of a third of the mean this kernel's own loss is 3% (813 / 788).
   const int grid = s.B * s.H * ((s.N + kTile - 1) / kTile);
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -454,7 +461,7 @@ hipError_t launch_fwd_bf16(const Shape& s, const FwdArgs& a, hipStream_t stream)
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   const int full = grid / (4 * cus), rest = grid % (4 * cus);
-  if (rest == 0 || 14 * full + 65 * rest / (4 * cus) > 58)
+  if (a.kmax < s.nb && (rest == 0 || 14 * full + 65 * rest / (4 * cus) > 58))
     return launch_fwd_bf16_wave(s, a, stream);
   Params p;
   p.q = static_cast<const uint16_t*>(a.q);

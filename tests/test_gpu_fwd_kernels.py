@@ -1,7 +1,8 @@
 """The two kernels of the bf16 forward (four waves per 64-row query tile, or
-one) give the same bytes, and each of their edge paths meets the oracle.
+one) give the same bytes, the edge paths of the one-wave kernel meet the oracle,
+and it is not given lists of which one may be far longer than the others.
 
-Every case here is a launch of 1024 tiles (4 per CU of 256 CUs), which the
+Every case of the edges is a launch of 1024 tiles (4 per CU of 256 CUs), which the
 rule gives to the one-wave kernel; the same heads computed alone are 16-tile
 launches, which take the four-wave one."""
 import numpy as np
@@ -34,10 +35,11 @@ def _gpu():
     torch.cuda.synchronize()
 
 
-def one_wave(tiles):
-    """The forward's rule: rounds of 4 tiles per CU and the last one's share."""
+def one_wave(tiles, kmax, nb):
+    """The forward's rule: rounds of 4 tiles per CU and the last one's share,
+    and lists that cannot be the whole row."""
     full, rest = divmod(tiles, 4 * CUS)
-    return rest == 0 or 14 * full + 65 * rest // (4 * CUS) > 58
+    return kmax < nb and (rest == 0 or 14 * full + 65 * rest // (4 * CUS) > 58)
 
 
 def make_lists(kind, B, H, nb, kmax, seed):
@@ -111,9 +113,10 @@ CASES = [
 def test_one_wave_kernel_edges(B, H, N, block, kind, token_major, causal, qk_scale, growing):
     seed = 31 * N + block + len(kind)
     nb = O.block_count(N, block)
-    assert one_wave(B * H * -(-N // 64)) and not one_wave(-(-N // 64))
+    kmax, tiles = max(2, nb - 2), -(-N // 64)
+    assert one_wave(B * H * tiles, kmax, nb) and not one_wave(tiles, kmax, nb)
     q, k, v = tensors(B, H, N, token_major, seed, qk_scale, growing)
-    idx, cnt = make_lists(kind, B, H, nb, max(2, nb - 2), seed)
+    idx, cnt = make_lists(kind, B, H, nb, kmax, seed)
     di, dc = idx.to(DEV), cnt.to(DEV)
     order = sa.sparse_attn_schedule(dc, N, idx.shape[-1], block=block)
     kw = dict(block=block, causal=causal)
@@ -153,9 +156,52 @@ def test_rows_of_equal_values_come_back_exactly(qk_scale):
     v.fill_(1.0)
     idx, cnt = make_lists("full", B, H, 16, 13, 6)
     idx, cnt = idx.to(DEV), cnt.to(DEV)
-    assert one_wave(B * H * 16)
+    assert one_wave(B * H * 16, 13, 16)
     o, _ = sa.sparse_attn_fwd(q, k, v, idx, cnt)
     assert torch.equal(o, torch.ones_like(o))
     o, _ = sa.sparse_attn_fwd(q[:, :2], k[:, :2], v[:, :2], idx[:, :2].contiguous(),
                               cnt[:, :2].contiguous())
     assert torch.equal(o, torch.ones_like(o))
+
+
+def _us(f, reps=10):
+    f()
+    torch.cuda.synchronize()
+    best = float("inf")
+    for _ in range(3):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(reps):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / reps)
+    return best
+
+
+def test_one_long_list_does_not_hold_up_the_launch():
+    """A whole-head budget may keep one row whole.  The other 1022 tiles' work
+    (about 105 us) runs beside such a list, so the call takes about the time
+    of one long list alone on the four-wave kernel: 1.05 times it measured, and
+    2.2 with one wave per tile."""
+    H, N, keep = 2, 32768, 36
+    nb = N // 64
+    g = torch.Generator(device=DEV).manual_seed(9)
+    q, k, v = (torch.randn(1, H, N, 128, generator=g, device=DEV).bfloat16() for _ in range(3))
+    cnt = torch.full((1, H, nb), keep)
+    cnt[..., 0] = nb
+    first = (torch.arange(nb) - keep // 2).clamp(0, nb - keep)
+    j = torch.arange(nb)
+    idx = torch.where(j < keep, first[:, None] + j, -1)
+    idx[0] = j
+    idx = idx.int().expand(1, H, nb, nb).contiguous().to(DEV)
+    cnt = cnt.int().to(DEV)
+    order = sa.sparse_attn_schedule(cnt, N, nb)
+    assert not one_wave(H * nb, nb, nb) and one_wave(H * nb, nb - 1, nb)
+    both = _us(lambda: sa.sparse_attn_fwd(q, k, v, idx, cnt, order=order))
+    only = cnt[:, :1].clone()  # one head: 512 tiles
+    only[..., 1:] = 0
+    head = [t[:, :1].contiguous() for t in (q, k, v, idx)]
+    alone = _us(lambda: sa.sparse_attn_fwd(*head, only))
+    print(f"  {both:.0f} us, the long list alone {alone:.0f}")
+    assert both < 1.5 * alone, (both, alone)
