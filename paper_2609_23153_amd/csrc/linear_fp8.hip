@@ -525,36 +525,44 @@ __global__ __launch_bounds__(256) void linear_w8a8_kernel(LinArgs a) {
 // ---- product, few tokens ----------------------------------------------------
 //
 // With few tokens the 256 x 256 tiles leave most CUs idle (512 tokens x 5120
-// channels: 40 tiles on 256 CUs).  Here a workgroup owns a small tile of
-// (32 TN channels) x (32 TM tokens) and its 4 waves split K between them:
-// wave w takes the 128-byte K slices w, w + 4, ... of every row of the tile,
-// each through an LDS ring of its own, so the main loop has no barrier.  The
-// four partial tiles are added in LDS in a fixed order (deterministic).
-// Bound by LDS and L2 -> LDS bandwidth: a slice of R rows costs 2 R LDS
-// cycles (written and read once) against 8 TN TM MFMA cycles per CU, so the
-// tile grows with the number of tokens (see launch_linear_w8a8).
+// channels: 40 tiles on 256 CUs).  Here a workgroup of four waves owns a small
+// tile of (32 TN channels) x (32 TM tokens), wave w < TN TM the products of its
+// w-th 32 x 32 part over all of K, in the order of the other kernels, so that a
+// token's result does not depend on the number of tokens.  All four waves copy:
+// a stage is kSL 128-byte K slices of the tile's rows, a quarter each, in a ring
+// of as many stages as fit; a step's products run on fragments in registers
+// while those of the next stage are read, and at the barrier that ends step s
+// stage s + 2 has landed; step s copies stage s + kDepth over stage s.
+// Bound by the chain of products (5120 deep: 80 of 64 cycles, 2.1 us) and the
+// latencies around it, of the launch and of a barrier every two slices: 5120 ->
+// 5120, us: 1 token 7.7, 64 9.2, 128 11.2 (with K split over the waves and the
+// partials added at the end, in another order: 5.7, 7.3, 11.3; one wave per
+// tile, which may have 63 KB of copies in flight: 12.2, 18.3, 27.9).
+constexpr int kSL = 2;
+
 template <int TN, int TM>
-struct SplitTile {
+struct SmallTile {
   static constexpr int kRows = 32 * (TN + TM);
-  static constexpr int kSlice = kRows * kBK;                    // bytes of one K slice
-  static constexpr int kDepth = 36864 / kSlice;  // ring slots per wave
-  static constexpr int kRing = kDepth * kSlice;
-  static constexpr int kPad = 32 * TN + 4;                      // floats per staged token row
-  static constexpr int kStage = 32 * TM * kPad * 4;             // one wave's partial tile
-  static constexpr int kLds = 4 * (kRing > kStage ? kRing : kStage);
+  static constexpr int kSlice = kRows * kBK;         // bytes of one K slice
+  static constexpr int kStage = kSL * kSlice;
+  static constexpr int kDepth = 147456 / kStage;     // ring stages
+  static constexpr int kDmas = kSL * (TN + TM);      // copies per wave and stage, 8 rows each
+  static constexpr int kPad = 36;                    // floats per staged token row of a part
+  static constexpr int kLds = kDepth * kStage;
+  static_assert(TN * TM <= 4 && 4 * 32 * kPad * 4 <= kLds, "the parts are staged in the ring");
+  static_assert(kDepth >= 2 && kDepth <= 9, "every count of stages in flight has its wait");
 };
 
-// Eight channels n.. of token m from the fp32 sums in LDS (W partial tiles of
-// `stride` floats, added in order): scales, bias, bf16, one 16-byte store.
-template <int W>
-__device__ __forceinline__ void store_cell(const LinArgs& a, const float* src, int stride, int m,
-                                           int n) {
-  f32x4 s0 = *reinterpret_cast<const f32x4*>(src), s1 = *reinterpret_cast<const f32x4*>(src + 4);
-#pragma unroll
-  for (int w = 1; w < W; ++w) {
-    s0 += *reinterpret_cast<const f32x4*>(src + w * stride);
-    s1 += *reinterpret_cast<const f32x4*>(src + w * stride + 4);
-  }
+template <int I>
+struct Const {
+  static constexpr int value = I;
+};
+
+// Eight channels n.. of token m from the fp32 sums in LDS: scales, bias, bf16,
+// one 16-byte store.
+__device__ __forceinline__ void store_cell(const LinArgs& a, const float* src, int m, int n) {
+  const f32x4 s0 = *reinterpret_cast<const f32x4*>(src);
+  const f32x4 s1 = *reinterpret_cast<const f32x4*>(src + 4);
   const float sx = a.sx[m];
   u32x4 o;
 #pragma unroll
@@ -572,9 +580,9 @@ __device__ __forceinline__ void store_cell(const LinArgs& a, const float* src, i
 }
 
 template <int TN, int TM>
-__global__ __launch_bounds__(256) void linear_split_kernel(LinArgs a) {
-  using T = SplitTile<TN, TM>;
-  constexpr int kDmas = T::kRows / 8;  // copies per slice, 8 rows each
+__global__ __launch_bounds__(256) void linear_small_kernel(LinArgs a) {
+  using T = SmallTile<TN, TM>;
+  constexpr int kDmas = T::kDmas, kDepth = T::kDepth;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[T::kLds];
 
   // XCD x (workgroup id mod 8) takes a contiguous run of the channel-major
@@ -589,120 +597,166 @@ __global__ __launch_bounds__(256) void linear_split_kernel(LinArgs a) {
   const int lane = threadIdx.x & 63, g = lane >> 5, l32 = lane & 31;
   const auto wr = make_rsrc(a.w + (int64_t)n0 * a.ldw, (uint32_t)(min(32 * TN, a.N - n0) * a.ldw));
   const auto xr = make_rsrc(a.x + (int64_t)m0 * a.ldx, (uint32_t)(min(32 * TM, a.M - m0) * a.ldx));
-  uint8_t* ring = lds + wv * T::kRing;
-  const uint32_t ring_addr = lds_addr(lds) + (uint32_t)(wv * T::kRing);
 
-  // per-lane byte offsets of the copies: 8 rows of 128 bytes each, lane l in
-  // slot l % 8 of row l / 8 (the swizzle is an involution; rows past N or M
-  // are out of the resource's range and read zero)
+  // copies of this wave, 8 rows each, lane l in slot l % 8 of row l / 8 (the
+  // swizzle is an involution; rows past N or M are out of the resource's range
+  // and read zero): a quarter of the stage's weight rows, then of its
+  // activation rows, copy i of a kind in slice i / TN (i / TM)
+  constexpr int kW = TN * kSL;
   uint32_t off[kDmas];
 #pragma unroll
   for (int i = 0; i < kDmas; ++i) {
-    const int r = 8 * i + (lane >> 3);
-    const int c = swz128(r, lane & 7);
-    off[i] = r < 32 * TN ? (uint32_t)(r * a.ldw + 16 * c)
-                         : (uint32_t)((r - 32 * TN) * a.ldx + 16 * c);
+    const bool w = i < kW;
+    const int per = w ? TN : TM, j = w ? i : i - kW;
+    const int r = 8 * (wv * per + j % per) + (lane >> 3);
+    off[i] = (uint32_t)(r * (w ? a.ldw : a.ldx) + 16 * swz128(w ? r : 32 * TN + r, lane & 7));
   }
-  const int S = a.K / kBK;
-  const int mine = S > wv ? (S - wv + 3) >> 2 : 0;  // slices of this wave
-  auto copy = [&](int s) {  // the wave's slice s into ring slot s % kDepth
-    const uint32_t base = ring_addr + (uint32_t)((s % T::kDepth) * T::kSlice);
-    const uint32_t k0 = (uint32_t)((4 * s + wv) * kBK);
+  const int S = a.K / kBK, G = (S + kSL - 1) / kSL;
+  const uint32_t cbase = lds_addr(lds);
+  // copy i of stage n, into ring stage `at` (slices past K: the last one again,
+  // which is not read)
+  auto copy = [&](int n, int at, int i) __attribute__((always_inline)) {
+    const bool w = i < kW;
+    const int per = w ? TN : TM, j = w ? i : i - kW, u = j / per;
+    const int row = u * T::kRows + (w ? 0 : 32 * TN) + 8 * (wv * per + j % per);
+    dma16(cbase + (uint32_t)(at * T::kStage + row * kBK), w ? wr : xr, off[i],
+          (uint32_t)(min(kSL * n + u, S - 1) * kBK));
+  };
+  // waits until at most this wave's copies of `later` stages are in flight
+  auto landed = [&](int later) __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+#define SA_LANDED(n) \
+  if (later == n) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(n < kDepth ? n * kDmas : 0) : "memory")
+    SA_LANDED(8);
+    else SA_LANDED(7);
+    else SA_LANDED(6);
+    else SA_LANDED(5);
+    else SA_LANDED(4);
+    else SA_LANDED(3);
+    else SA_LANDED(2);
+    else SA_LANDED(1);
+    else SA_LANDED(0);
+#undef SA_LANDED
+  };
+
+  const bool mine = wv < TN * TM;
+  const int pi = mine ? wv / TM : 0, pj = mine ? wv - pi * TM : 0;  // this wave's part
+  const int sw = (l32 >> 1) & 7;  // the swizzle depends on row % 16 only
+  const uint8_t* arow = lds + (32 * pi + l32) * kBK;
+  const uint8_t* brow = lds + (32 * TN + 32 * pj + l32) * kBK;
+  f32x16 acc;
 #pragma unroll
-    for (int i = 0; i < kDmas; ++i) {
-      if (8 * i < 32 * TN)
-        dma16(base + 8 * i * kBK, wr, off[i], k0);
-      else
-        dma16(base + 8 * i * kBK, xr, off[i], k0);
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  i32x8 fa[2][2 * kSL], fb[2][2 * kSL];  // fragments of a stage, by its parity
+  // the fragments of K step u (64 deep) of the stage in ring stage `at`
+  auto read = [&](int at, int u, i32x8& f, i32x8& h) __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int o = at * T::kStage + (u >> 1) * T::kSlice +
+                    16 * ((4 * (u & 1) + 2 * g + p) ^ sw);
+      const u32x4 va = *reinterpret_cast<const u32x4*>(arow + o);
+      const u32x4 vb = *reinterpret_cast<const u32x4*>(brow + o);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        f[4 * p + e] = (int)va[e];
+        h[4 * p + e] = (int)vb[e];
+      }
+    }
+  };
+  auto product = [&](const i32x8& f, const i32x8& h) __attribute__((always_inline)) {
+    acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(f, h, acc, 0, 0, 0, kOneE8m0, 0, kOneE8m0);
+  };
+  // Stage n, whose fragments are in fa / fb [P] of a wave with products: these,
+  // and behind each of them a part of the reads of stage n + 1; the copies of
+  // stage n + kDepth.
+  int slot = 0;  // n % kDepth
+  auto step = [&](int n, auto parity, auto products, auto steady) __attribute__((always_inline)) {
+    constexpr int P = decltype(parity)::value;
+    const int at = slot;
+    slot = slot + 1 == kDepth ? 0 : slot + 1;
+    if (decltype(steady)::value || n + kDepth < G) {
+#pragma unroll
+      for (int i = 0; i < kDmas; ++i) copy(n + kDepth, at, i);
+    }
+    if (decltype(products)::value) {
+#pragma unroll
+      for (int u = 0; u < 2 * kSL; ++u) {
+        product(fa[P][u], fb[P][u]);
+        read(slot, u, fa[1 - P][u], fb[1 - P][u]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wait_lgkm0();
+    }
+    if (decltype(steady)::value) landed(kDepth - 2);
+    else if (n + 2 < G) landed(min(G, n + kDepth + 1) - n - 3);
+    barrier_keep_loads();  // stage n + 2 has landed, every wave is done with n + 1
+  };
+  auto last = [&](int n, auto parity) __attribute__((always_inline)) {
+    constexpr int P = decltype(parity)::value;
+#pragma unroll
+    for (int u = 0; u < 2 * kSL; ++u)
+      if (kSL * n + (u >> 1) < S) product(fa[P][u], fb[P][u]);  // the slices left of K
+  };
+  auto run = [&](auto products) __attribute__((always_inline)) {
+    constexpr bool kProducts = decltype(products)::value;
+    if (kProducts) {
+#pragma unroll
+      for (int u = 0; u < 2 * kSL; ++u) read(0, u, fa[0][u], fb[0][u]);
+      wait_lgkm0();
+    }
+    if (1 < G) landed(min(G, kDepth) - 2);
+    barrier_keep_loads();
+    int n = 0;
+    for (; n + 1 + kDepth < G; n += 2) {
+      step(n, Const<0>{}, products, Const<1>{});
+      step(n + 1, Const<1>{}, products, Const<1>{});
+    }
+    for (; n + 2 < G; n += 2) {
+      step(n, Const<0>{}, products, Const<0>{});
+      step(n + 1, Const<1>{}, products, Const<0>{});
+    }
+    if (n + 1 < G) {
+      step(n, Const<0>{}, products, Const<0>{});
+      if (kProducts) last(n + 1, Const<1>{});
+    } else if (kProducts) {
+      last(n, Const<0>{});
     }
   };
 
-  f32x16 acc[TN][TM];
 #pragma unroll
-  for (int i = 0; i < TN; ++i)
+  for (int n = 0; n < kDepth; ++n)
+    if (n < G) {
 #pragma unroll
-    for (int j = 0; j < TM; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      for (int i = 0; i < kDmas; ++i) copy(n, n, i);
+    }
+  landed(min(G, kDepth) - 1);
+  barrier_keep_loads();
+  if (mine) run(Const<1>{});
+  else run(Const<0>{});
 
+  // each part as [token][channel], then 8 channels of a token per store (no
+  // copy is in flight, and every wave is past its reads)
+  if (!mine) return;  // no barrier below
+  float* st = reinterpret_cast<float*>(lds) + wv * 32 * T::kPad;
 #pragma unroll
-  for (int s = 0; s < T::kDepth; ++s)
-    if (s < mine) copy(s);
-  for (int s = 0; s < mine; ++s) {
-    // the slice has landed when at most the copies of the later ones are in flight
-    __builtin_amdgcn_sched_barrier(0);
-    const int later = min(mine - 1 - s, T::kDepth - 1);
-    if (later == 0)
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else if (later == 1)
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kDmas) : "memory");
-    else if (later == 2)
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kDmas < 63 ? 2 * kDmas : 63) : "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * kDmas < 63 ? 3 * kDmas : 63) : "memory");
-    const uint8_t* sb = ring + (s % T::kDepth) * T::kSlice;
-    i32x8 fa[2][TN], fb[2][TM];
-    const int sw = (l32 >> 1) & 7;  // the swizzle depends on row % 16 only
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int f = 0; f < TN + TM; ++f)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const u32x4 v = *reinterpret_cast<const u32x4*>(sb + (32 * f + l32) * kBK +
-                                                          16 * ((4 * ks + 2 * g + h) ^ sw));
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (f < TN)
-              fa[ks][f < TN ? f : 0][4 * h + e] = (int)v[e];
-            else
-              fb[ks][f < TN ? 0 : f - TN][4 * h + e] = (int)v[e];
-          }
-        }
-    wait_lgkm0();  // the slot is free
-    if (s + T::kDepth < mine) copy(s + T::kDepth);
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-              fa[ks][i], fb[ks][j], acc[i][j], 0, 0, 0, kOneE8m0, 0, kOneE8m0);
+  for (int q = 0; q < 4; ++q) {
+    const f32x4 v = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    *reinterpret_cast<f32x4*>(st + l32 * T::kPad + 8 * q + 4 * g) = v;
   }
-
-  // partial tiles [token][channel] of the four waves, added in wave order
-  __syncthreads();  // every wave's ring is done with (its copies have been waited for)
-  float* st = reinterpret_cast<float*>(lds + wv * T::kStage);
+  wait_lgkm0();  // each wave reads back only what it wrote
 #pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int j = 0; j < TM; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2],
-                         acc[i][j][4 * q + 3]};
-        *reinterpret_cast<f32x4*>(st + (32 * j + l32) * T::kPad + 32 * i + 8 * q + 4 * g) = v;
-      }
-  __syncthreads();
-  constexpr int kChunks = 4 * TN;          // 8-channel chunks of a token row
-  constexpr int kCells = 32 * TM * kChunks;
-#pragma unroll
-  for (int c0 = 0; c0 < kCells; c0 += 256) {
-    const int cell = c0 + threadIdx.x;
-    if (kCells < 256 && cell >= kCells) break;
-    const int r = cell / kChunks, c = cell - r * kChunks;
-    const int m = m0 + r, n = n0 + 8 * c;
-    if (m >= a.M || n >= a.N) continue;
-    store_cell<4>(a, reinterpret_cast<const float*>(lds) + r * T::kPad + 8 * c, T::kStage / 4, m, n);
+  for (int p = 0; p < 2; ++p) {
+    const int r = 16 * p + (lane >> 2), c = lane & 3;
+    const int m = m0 + 32 * pj + r, n = n0 + 32 * pi + 8 * c;
+    if (m < a.M && n < a.N) store_cell(a, st + r * T::kPad + 8 * c, m, n);
   }
 }
 
 template <int TN, int TM>
-hipError_t launch_split(LinArgs a, hipStream_t stream) {
+hipError_t launch_small(LinArgs a, hipStream_t stream) {
   a.tiles_m = (a.M + 32 * TM - 1) / (32 * TM);
   a.tiles_n = (a.N + 32 * TN - 1) / (32 * TN);
-  linear_split_kernel<TN, TM><<<dim3((unsigned)(a.tiles_m * a.tiles_n)), 256, 0, stream>>>(a);
+  linear_small_kernel<TN, TM><<<dim3((unsigned)(a.tiles_m * a.tiles_n)), 256, 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -720,7 +774,7 @@ constexpr int kMidPad = 68;  // floats per staged token row of a wave's quarter
 
 __global__ __launch_bounds__(256) void linear_mid_kernel(LinArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t lds[4 * kMidStage];
-  const int tiles = a.tiles_m * a.tiles_n;  // XCD runs as in linear_split_kernel
+  const int tiles = a.tiles_m * a.tiles_n;  // XCD runs as in linear_small_kernel
   const int id = blockIdx.x, xcd = id & 7;
   const int t = xcd * (tiles >> 3) + min(xcd, tiles & 7) + (id >> 3);
   const int tn = t / a.tiles_m;
@@ -820,7 +874,7 @@ __global__ __launch_bounds__(256) void linear_mid_kernel(LinArgs a) {
   for (int p = 0; p < 8; ++p) {
     const int r = 8 * p + (lane >> 3), c = lane & 7;
     const int m = m0 + 64 * wm + r, n = n0 + 64 * wn + 8 * c;
-    if (m < a.M && n < a.N) store_cell<1>(a, st + r * kMidPad + 8 * c, 0, m, n);
+    if (m < a.M && n < a.N) store_cell(a, st + r * kMidPad + 8 * c, m, n);
   }
 }
 
@@ -873,22 +927,24 @@ hipError_t launch_linear_w8a8(const LinearIn& in, hipStream_t stream) {
   const int64_t T = (int64_t)a.tiles_m * a.tiles_n;
   // The kernel whose launch takes the least time: rounds of one workgroup per
   // CU times the time of a round, in units of about 0.5 us at K = 5120 (every
-  // round grows with K alike; measured, one round of each): 32 x 32 tiles 15,
-  // 32 x 64 19, 64 x 64 22, 128 x 128 46, 256 x 256 92 (the persistent kernel,
-  // which also wins a tie).  5120 -> 5120, us per launch before (256 x 256
-  // tiles only) and now: 32 tokens 45.9 -> 9.6, 128 47.3 -> 11.0, 350 48.9 ->
-  // 22.2, 512 50.6 -> 26.0; from 1024 on the 256 x 256 tiles are the faster ones.
+  // round grows with K alike; measured, one round of each): 32 x 32 tiles 16,
+  // 64 channels x 32 tokens 18, 64 x 64 22, 128 x 128 46, 256 x 256 92 (the
+  // persistent kernel, which also wins a tie).  All of them sum over K in the
+  // same order: the choice does not change a byte.  5120 -> 5120, us per launch
+  // with 256 x 256 tiles only and now: 32 tokens 46.3 -> 8.0, 128 47.7 -> 11.2,
+  // 350 48.3 -> 20.9, 512 50.7 -> 22.9; from 1024 on the 256 x 256 tiles are the
+  // faster ones.
   auto tiles = [&](int bn, int bm) {
     return ((in.N + bn - 1) / bn) * ((in.M + bm - 1) / bm);
   };
   auto cost = [&](int64_t n, int unit) { return (n + cus - 1) / cus * unit; };
   const int64_t big = cost(T, 92), mid = cost(tiles(kMidTile, kMidTile), 46),
-                s22 = cost(tiles(64, 64), 22), s12 = cost(tiles(32, 64), 19),
-                s11 = cost(tiles(32, 32), 15);
-  const int64_t split = s11 < s12 ? (s11 < s22 ? s11 : s22) : (s12 < s22 ? s12 : s22);
-  if (split < big && split <= mid) {
-    if (split == s22) return launch_split<2, 2>(a, stream);
-    return split == s12 ? launch_split<1, 2>(a, stream) : launch_split<1, 1>(a, stream);
+                s22 = cost(tiles(64, 64), 22), s21 = cost(tiles(64, 32), 18),
+                s11 = cost(tiles(32, 32), 16);
+  const int64_t small = s11 < s21 ? (s11 < s22 ? s11 : s22) : (s21 < s22 ? s21 : s22);
+  if (small < big && small <= mid) {
+    if (small == s22) return launch_small<2, 2>(a, stream);
+    return small == s21 ? launch_small<2, 1>(a, stream) : launch_small<1, 1>(a, stream);
   }
   if (mid < big) {
     a.tiles_m = (a.M + kMidTile - 1) / kMidTile;

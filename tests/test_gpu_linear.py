@@ -191,17 +191,35 @@ def test_linear_full_size(name, m_sub):
 
 
 @pytest.mark.parametrize("M,N,K,bias,pad_y", [
-    (1, 40, 256, True, 0),        # 32 x 32 tiles: 2 slices for 4 waves, ragged channels
-    (33, 5120, 640, True, 8),     # 32 x 64 tiles: 5 slices, waves of 2 and 1
+    (1, 40, 256, True, 0),        # 32 x 32 tiles: 2 slices, one stage, ragged channels
+    (20, 520, 2432, True, 0),     # 32 x 32 tiles: 19 slices, one stage more than the ring holds
+    (33, 5120, 640, True, 8),     # 64 x 32 tiles: 5 slices, half of the last stage
+    (90, 5128, 1792, False, 0),   # 64 x 32 tiles: 7 stages, one more than the ring holds
     (127, 5128, 1152, False, 0),  # 64 x 64 tiles: 9 slices, ragged in both
     (300, 8960, 256, True, 0),    # 128 x 128 tiles, 2 stages (fewer than the ring holds)
     (300, 8968, 896, False, 24),  # 128 x 128 tiles, 7 stages, ragged in both
 ])
 def test_linear_few_tokens(M, N, K, bias, pad_y):
     """Each tile size of the small-M dispatch at its edges: partial tiles,
-    fewer K slices than waves or ring slots, odd slice counts."""
+    fewer K slices than ring slots, odd slice counts."""
     y, a8, sa_, w8, sw, b = linear_case(M, N, K, seed=M + N + K, bias=bias, pad_y=pad_y)
     check_linear(y, a8, sa_, w8, sw, b, f"linear M{M} N{N} K{K}")
+
+
+@pytest.mark.parametrize("N,K", [(5120, 5120), (1032, 1152), (5120, 256), (13824, 640)])
+def test_linear_token_does_not_depend_on_their_number(N, K):
+    """Every tile size sums over K in the same order: a token's outputs are the
+    same bytes whichever kernel the number of tokens leads to.  Values spread
+    over many binades, so that fp32 sums in another order differ."""
+    g = torch.Generator(device=DEV).manual_seed(N + K)
+    wide = lambda r: (torch.randn(r, K, device=DEV, generator=g)
+                      * torch.exp(2.5 * torch.randn(r, K, device=DEV, generator=g))).bfloat16()
+    wq, sw = sa.sparse_attn_quant_rows_fp8(wide(N))
+    xq, sx = sa.sparse_attn_quant_rows_fp8(wide(2048))
+    ref = sa.sparse_attn_linear_w8a8(xq, sx, wq, sw)
+    for M in (1, 32, 33, 64, 96, 128, 200, 350, 512, 777, 1024, 1500):
+        y = sa.sparse_attn_linear_w8a8(xq[:M], sx[:M], wq, sw)
+        assert torch.equal(y.view(torch.int16), ref[:M].view(torch.int16)), M
 
 
 @pytest.mark.parametrize("rows,cols,pad", [
