@@ -43,6 +43,7 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
 
 constexpr int kRowsPerGroup = 4;   // one row per wave
 constexpr int kFewRows = 1024;
+constexpr int64_t kRowsPerLaunch = 1 << 23;
 
 // W waves per row, P 16-byte chunks per lane: rows of up to 512 * W * P
 // elements.  Bound by HBM when there are many rows (5120 columns x 75,600
@@ -883,22 +884,29 @@ __global__ __launch_bounds__(256) void linear_mid_kernel(LinArgs a) {
 hipError_t launch_quant_rows_fp8(const void* x, int64_t ldx, int64_t rows, int cols, uint8_t* q,
                                  float* scale, hipStream_t stream) {
   if (rows == 0) return hipSuccess;
-  const dim3 grid((unsigned)((rows + kRowsPerGroup - 1) / kRowsPerGroup));
-  const uint16_t* xp = static_cast<const uint16_t*>(x);
   const int nch = cols / 8;
-  // One row per workgroup, except for short rows in numbers that fill the chip
-  // (us, one wave per row / four: 1536 columns x 512 rows 3.0 / 2.4, x 2048
-  // 3.0 / 3.3; 5120 columns x 2048 rows 6.6 / 5.4, x 75,600 214 / 198).
-  const dim3 one((unsigned)rows);
-  if (nch <= 64 * 4 && (rows > kFewRows || nch <= 64))
-    quant_rows_kernel<4, 1><<<grid, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
-  else if (nch <= 256 * 3)
-    quant_rows_kernel<3, 4><<<one, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
-  else if (nch <= 256 * 8)
-    quant_rows_kernel<8, 4><<<one, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
-  else
-    quant_rows_stream_kernel<<<grid, 256, 0, stream>>>(xp, ldx, rows, cols, q, scale);
-  return hipGetLastError();
+  // (a launch takes fewer than 2^32 threads, 2^24 rows of one workgroup each;
+  // beyond, the runtime starts a part of it without an error)
+  for (int64_t r = 0; r < rows; r += kRowsPerLaunch) {
+    const int64_t n = rows - r < kRowsPerLaunch ? rows - r : kRowsPerLaunch;
+    const uint16_t* xp = static_cast<const uint16_t*>(x) + r * ldx;
+    uint8_t* qp = q + r * cols;
+    const dim3 grid((unsigned)((n + kRowsPerGroup - 1) / kRowsPerGroup)), one((unsigned)n);
+    // One row per workgroup, except for short rows in numbers that fill the chip
+    // (us, one wave per row / four: 1536 columns x 512 rows 3.0 / 2.4, x 2048
+    // 3.0 / 3.3; 5120 columns x 2048 rows 6.6 / 5.4, x 75,600 214 / 198).
+    if (nch <= 64 * 4 && (rows > kFewRows || nch <= 64))
+      quant_rows_kernel<4, 1><<<grid, 256, 0, stream>>>(xp, ldx, n, cols, qp, scale + r);
+    else if (nch <= 256 * 3)
+      quant_rows_kernel<3, 4><<<one, 256, 0, stream>>>(xp, ldx, n, cols, qp, scale + r);
+    else if (nch <= 256 * 8)
+      quant_rows_kernel<8, 4><<<one, 256, 0, stream>>>(xp, ldx, n, cols, qp, scale + r);
+    else
+      quant_rows_stream_kernel<<<grid, 256, 0, stream>>>(xp, ldx, n, cols, qp, scale + r);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_linear_w8a8(const LinearIn& in, hipStream_t stream) {

@@ -235,3 +235,26 @@ def test_quant_rows_dispatch_edges(rows, cols, pad):
     x, _, _ = W.linear_inputs(rows, cols, 4, seed=rows + cols)
     q, s = quant_gpu(x, pad)
     check_quant(x, q, s, f"quant {rows}x{cols} pad {pad}")
+
+
+def test_quant_rows_more_than_a_launch_holds():
+    """2^24 rows and a few: one workgroup of 256 threads per row would be 2^32
+    threads, more than a launch takes.  Rows around the launches' ends are the
+    codes of the same rows alone; all others are zero."""
+    rows, cols = (1 << 24) + 5, 2056
+    if torch.cuda.mem_get_info()[0] < 120e9:
+        pytest.skip("needs 120 GB of free GPU memory")
+    some = [0, 1, (1 << 23) - 1, 1 << 23, (1 << 24) - 1, 1 << 24, rows - 1]
+    g = torch.Generator(device=DEV).manual_seed(5)
+    few = torch.randn(len(some), cols, device=DEV, generator=g).bfloat16()
+    x = torch.zeros(rows, cols, dtype=torch.bfloat16, device=DEV)
+    x[some] = few
+    q, s = sa.sparse_attn_quant_rows_fp8(x)
+    del x
+    qf, sf = sa.sparse_attn_quant_rows_fp8(few)
+    assert torch.equal(q[some], qf) and torch.equal(s[some], sf)
+    zero = s == 2.0 ** -100 / 448
+    assert int((~zero).sum()) == len(some)
+    for lo in range(0, rows, 1 << 22):  # in parts: the comparison's own memory
+        n = int((q[lo:lo + (1 << 22)] != 0).any(1).sum())
+        assert n == sum(lo <= r < lo + (1 << 22) for r in some), lo
