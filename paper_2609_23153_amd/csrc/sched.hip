@@ -12,13 +12,15 @@
 // The cost classes are floor(log2(key tiles)), so the sort is a 16-bucket
 // stable partition (a counting sort) over chunks of 1024 tiles.  Up to
 // kOneChunks chunks it is one launch: every workgroup counts the classes of
-// all tiles itself (the list lengths come from L2, a few 8-bit counters per
-// thread), which takes less time than two further launches: 47,280 tiles 4.8
-// us (22 in three launches), 128 tiles 2.9 us (15).  Its work grows with the
-// square of the tiles, hence the limit.  Beyond, three launches: class counts
-// per chunk, one exclusive scan of the counts (classes descending, chunks
-// ascending), and a scatter that writes every tile straight into its launch
-// slot.
+// all tiles itself, work that grows with the square of the tiles.  Up to
+// kTwoChunks, two: class counts per chunk, and a scatter that writes every
+// tile straight into its launch slot, whose workgroups sum the counts
+// themselves.  Beyond, a scan of the counts (classes descending, chunks
+// ascending) between the two.  One / two / three launches, us, lists of equal
+// length (which one launch need not count) and of uneven ones: 128 tiles 2.2 and
+// 5.2 / 6.4 / 12.4; 8192 3.2 and 8.5 / 9.8 / 16.0; 12,288 3.5 and 10.2 / 9.8 /
+// 16.0; 47,280 4.9 and 20.8 / 10.5 / 16.4 (blocks of 128: 31.8 / 11.7 / 17.4);
+// 188,416 10.6 and 62.9 / 11.4 / 18.0; 500,736 - / 15 / 23.
 #include <mutex>
 
 #include "common.h"
@@ -148,16 +150,56 @@ __global__ __launch_bounds__(kScanThreads) void sched_scan_kernel(int chunks,
   }
 }
 
+// In lane c of a row of 16: the sum of x over the classes above c.
+__device__ __forceinline__ int above_sum(int x) {
+  int above = x;
+#define SA_SHL(n) above += __builtin_amdgcn_update_dpp(0, above, 0x100 + n, 0xF, 0xF, true)
+  SA_SHL(1);
+  SA_SHL(2);
+  SA_SHL(4);
+  SA_SHL(8);
+#undef SA_SHL
+  return above - x;
+}
+
 // Each tile's sorted position = class start + class-c tiles in earlier chunks
 // + class-c tiles before it in this chunk; written to order[slot(position)].
+// SCANNED: counts as sched_scan_kernel leaves them; otherwise as
+// sched_count_kernel does, and every workgroup sums them itself.
+template <bool SCANNED>
 __global__ __launch_bounds__(kSortThreads) void sched_scatter_kernel(
     SchedArgs a, const int32_t* __restrict__ counts, int32_t* __restrict__ order) {
   __shared__ int run[kClasses];
   __shared__ int wave_cnt[kSortThreads / kWave][kClasses];
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-  if (t < kClasses)
-    run[t] = counts[(int64_t)a.chunks * kClasses + t] +
-             counts[(int64_t)blockIdx.x * kClasses + t];
+  if (SCANNED) {
+    if (t < kClasses)
+      run[t] = counts[(int64_t)a.chunks * kClasses + t] +
+               counts[(int64_t)blockIdx.x * kClasses + t];
+  } else {
+    constexpr int kParts = kSortThreads / kClasses;
+    __shared__ int part[2][kParts][kClasses];
+    const int c = t & (kClasses - 1), p = t / kClasses;
+    int early = 0, all = 0;
+#pragma unroll 4
+    for (int ch = p; ch < a.chunks; ch += kParts) {
+      const int n = counts[ch * kClasses + c];
+      all += n;
+      early += ch < (int)blockIdx.x ? n : 0;
+    }
+    part[0][p][c] = early;
+    part[1][p][c] = all;
+    __syncthreads();
+    if (t < kClasses) {
+      early = all = 0;
+#pragma unroll
+      for (int q = 0; q < kParts; ++q) {
+        early += part[0][q][t];
+        all += part[1][q][t];
+      }
+      run[t] = above_sum(all) + early;
+    }
+  }
   const uint64_t below = lanes_below_mask();
   for (int m = 0; m < kChunk / kSortThreads; ++m) {
     // tiles of round m in index order: wave w holds the w-th 64 of them
@@ -212,7 +254,8 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
 // latency of the loads and of the launch.
 constexpr int kOneThreads = kChunk;
 constexpr int kOneWaves = kOneThreads / kWave;
-constexpr int kOneChunks = 96;
+constexpr int kOneChunks = 8;
+constexpr int kTwoChunks = 512;
 
 __global__ __launch_bounds__(kOneThreads) void sched_one_kernel(SchedArgs a,
                                                                 int32_t* __restrict__ order) {
@@ -272,15 +315,7 @@ __global__ __launch_bounds__(kOneThreads) void sched_one_kernel(SchedArgs a,
       all += (int)(wsum[w][1][word] >> sh & 0xffffu);
     }
     all += early;
-    // tiles of costlier classes: the sum over the higher lanes of this row of 16
-    int above = all;
-#define SA_SHL(n) above += __builtin_amdgcn_update_dpp(0, above, 0x100 + n, 0xF, 0xF, true)
-    SA_SHL(1);
-    SA_SHL(2);
-    SA_SHL(4);
-    SA_SHL(8);
-#undef SA_SHL
-    int pos = above - all + early;
+    int pos = above_sum(all) + early;
 #pragma unroll
     for (int w = 0; w < kOneWaves; ++w) {
       const int n = base[w][t];
@@ -353,10 +388,14 @@ hipError_t launch_schedule(const Shape& s, const int32_t* cnt, int kmax, int32_t
   sched_count_kernel<<<a.chunks, kSortThreads, 0, stream>>>(a, counts);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (a.chunks <= kTwoChunks) {
+    sched_scatter_kernel<false><<<a.chunks, kSortThreads, 0, stream>>>(a, counts, order);
+    return hipGetLastError();
+  }
   sched_scan_kernel<<<1, kScanThreads, 0, stream>>>(a.chunks, counts);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  sched_scatter_kernel<<<a.chunks, kSortThreads, 0, stream>>>(a, counts, order);
+  sched_scatter_kernel<true><<<a.chunks, kSortThreads, 0, stream>>>(a, counts, order);
   return hipGetLastError();
 }
 

@@ -451,3 +451,49 @@ def test_fwd_every_tile_of_every_launch_group(H, N, block):
     o2, l2 = sa.sparse_attn_fwd(qd, kd, vd, idx, cnt, block=block)
     torch.cuda.synchronize()
     assert torch.equal(o1, o2) and torch.equal(l1, l2) and torch.isfinite(o1.float()).all()
+
+
+@pytest.mark.parametrize("H,nb,block", [
+    (16, 512, 64),     # 8192 tiles: the most for one launch
+    (3, 2731, 64),     # 8193: the fewest for two
+    (5, 820, 128),     # 8200, two per query block
+    (1024, 512, 64),   # 524,288: the most for two
+    (1025, 512, 64),   # 524,800: three
+])
+def test_launch_order_at_the_edges_of_its_launches(H, nb, block):
+    g = torch.Generator().manual_seed(nb)
+    cnt = torch.randint(0, 600, (1, H, nb), generator=g, dtype=torch.int32)
+    N, kmax = nb * block, 512
+    order = sa.sparse_attn_schedule(cnt.to(DEV), N, kmax, block=block)
+    check_launch_order(order.cpu().numpy(), cnt.numpy(), kmax, N, block, f"{H}x{nb}")
+    static = sa.sparse_attn_schedule_static(cnt.to(DEV), N, kmax, torch.empty_like(order),
+                                            block=block)
+    assert torch.equal(static, order)
+
+
+def test_launch_order_of_uneven_lists_takes_no_longer():
+    """Counting the classes of every tile in every workgroup grows with the
+    square of the tiles: 47,280 tiles of uneven lists took 32 us that way, of
+    equal ones (which need no count) 4.  By chunks both take 12."""
+    H, nb, block = 40, 591, 128
+    g = torch.Generator().manual_seed(1)
+    even = torch.full((1, H, nb), 36, dtype=torch.int32, device=DEV)
+    uneven = torch.randint(0, 500, (1, H, nb), generator=g, dtype=torch.int32).to(DEV)
+    order = torch.empty(H * nb * 2, dtype=torch.int32, device=DEV)
+
+    def us(cnt):
+        best = float("inf")
+        for _ in range(4):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(30):
+                sa.sparse_attn_schedule_static(cnt, nb * block, 512, order, block=block)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 30 * 1e3)
+        return best
+
+    us(even)
+    a, b = us(even), us(uneven)
+    say(f"  equal lists {a:.1f} us, uneven {b:.1f}")
+    assert b < 1.7 * a, (a, b)
