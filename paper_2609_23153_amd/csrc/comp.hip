@@ -299,14 +299,18 @@ __global__ __launch_bounds__(256, 2) void comp_state_kernel(StateArgs a) {
 // C^T[bh][c][d][r] of causal chunk c = sum over the chunks c2 of its window
 // [c - window + 1, c] (all up to c for window 0), in ascending order, of
 // T_c2 = the sum of c2's sub-chunk partials in order.  Without a window there
-// is one chunk.  Each workgroup sums 256 of a head's elements, for every c; 8
-// partials are loaded ahead of their additions: one load in flight per thread
-// left them bound by latency (the state of 3 heads x 111600 tokens 79 ->
-// 59 us, 2 x 65536 50 -> 34, 40 x 75600 407 -> 390).
+// is one chunk.  Each workgroup sums 256 of a head's elements, for every c;
+// AHEAD partials are loaded before their additions: one load in flight per
+// thread left chunks of many partials bound by latency (AHEAD 1 / 8: the state
+// of 3 heads x 111600 tokens 79 / 59 us, 2 x 65536 50 / 34, 40 x 75600 407 /
+// 390), while chunks of fewer pay for the longer code (2 x 65536 in causal
+// chunks of 128: 200 / 214, 3 x 20000 in chunks of 64: 214 / 234).
+constexpr int kAhead = 8;
+
+template <int AHEAD>
 __global__ __launch_bounds__(256) void comp_reduce_kernel(const float* __restrict__ partial,
                                                           int nc, int nsub, int window,
                                                           float* __restrict__ state) {
-  constexpr int kAhead = 8;
   const int bh = blockIdx.x;
   const int e = blockIdx.y * 256 + threadIdx.x;
   const float* src = partial + (int64_t)bh * nc * nsub * kStateElems + e;
@@ -316,17 +320,18 @@ __global__ __launch_bounds__(256) void comp_reduce_kernel(const float* __restric
   const int d = 32 * dt + 8 * (reg >> 2) + 4 * (lane >> 5) + (reg & 3);
   float* dst = state + (int64_t)bh * nc * kStateElems + d * kRank + r;
   auto chunk_sum = [&](int c2) {
-    const float* p = src + (int64_t)c2 * nsub * kStateElems;
     float t = 0.f;
     int u = 0;
-    for (; u + kAhead <= nsub; u += kAhead) {
-      float x[kAhead];
+    if (AHEAD > 1)
+      for (; u + AHEAD <= nsub; u += AHEAD) {
+        float x[AHEAD];
 #pragma unroll
-      for (int i = 0; i < kAhead; ++i) x[i] = p[(int64_t)(u + i) * kStateElems];
+        for (int i = 0; i < AHEAD; ++i)
+          x[i] = src[((int64_t)c2 * nsub + u + i) * kStateElems];
 #pragma unroll
-      for (int i = 0; i < kAhead; ++i) t += x[i];
-    }
-    for (; u < nsub; ++u) t += p[(int64_t)u * kStateElems];
+        for (int i = 0; i < AHEAD; ++i) t += x[i];
+      }
+    for (; u < nsub; ++u) t += src[((int64_t)c2 * nsub + u) * kStateElems];
     return t;
   };
   if (window == 0) {  // running prefix: the same additions as the direct sums
@@ -634,8 +639,12 @@ hipError_t launch_comp_state(const Shape& s, const CompStateIn& in, float* state
   comp_state_kernel<<<dim3(s.B * s.H, a.nc * a.nsub), 256, 0, stream>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  comp_reduce_kernel<<<dim3(s.B * s.H, kReduceSplit), 256, 0, stream>>>(
-      a.partial, a.nc, a.nsub, s.causal_chunk > 0 ? s.causal_window : 0, state);
+  if (a.nsub < kAhead)
+    comp_reduce_kernel<1><<<dim3(s.B * s.H, kReduceSplit), 256, 0, stream>>>(
+        a.partial, a.nc, a.nsub, s.causal_chunk > 0 ? s.causal_window : 0, state);
+  else
+    comp_reduce_kernel<kAhead><<<dim3(s.B * s.H, kReduceSplit), 256, 0, stream>>>(
+        a.partial, a.nc, a.nsub, s.causal_chunk > 0 ? s.causal_window : 0, state);
   return hipGetLastError();
 }
 
