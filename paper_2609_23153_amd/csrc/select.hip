@@ -1233,12 +1233,12 @@ __global__ __launch_bounds__(256) void row_top1_kernel(const double* __restrict_
 
 // Histogram of the next 8-bit digit (bits shift..shift+7) of the order keys
 // of the remaining pairs that match the prefix found so far.  Blocks of 4
-// rows, one LDS add per pair: finding equal digits with ballots to add them at
-// once takes longer, except where a whole wave has one digit, and there it is
-// equal (the selection of 12 heads x 512 x 512: 182 -> 137 us together with the
-// passes left out, 5 x 1744 x 1744: 694 -> 489, all scores equal: 69 -> 69;
-// picking the digit in the pass's last workgroup instead of a launch needs
-// fences that cost more, 466).
+// rows, one LDS add per pair, or one for the wave where all its pairs have one
+// digit (64 adds to one word take 64 turns: 12 heads x 512 x 512 equal scores,
+// 10% kept, 206 -> 154 us).  Finding every group of equal digits with ballots
+// takes longer (12 heads x 512 x 512: 182 -> 137 us together with the passes
+// left out, 5 x 1744 x 1744: 694 -> 489; picking the digit in the pass's last
+// workgroup instead of a launch needs fences that cost more, 466).
 __global__ __launch_bounds__(256) void head_hist_kernel(const double* __restrict__ scores, int nb,
                                                         HeadWs w, int shift) {
   __shared__ uint32_t h[kBins];
@@ -1254,10 +1254,19 @@ __global__ __launch_bounds__(256) void head_hist_kernel(const double* __restrict
     const int64_t row = (int64_t)bh * nb + i;
     const double* s = scores + row * nb;
     const int skip = w.top1[row];
-    for (int j = lane; j < nb; j += kWave) {
-      const uint64_t key = order_key(s[j]);
-      if (j != skip && (key & mask) == (prefix & mask))
-        atomicAdd(&h[(uint32_t)(key >> shift) & (kBins - 1)], 1u);
+    for (int j0 = 0; j0 < nb; j0 += kWave) {
+      const int j = j0 + lane;
+      const uint64_t key = j < nb ? order_key(s[j]) : 0ull;
+      const uint32_t bin = (uint32_t)(key >> shift) & (kBins - 1);
+      const bool act = j < nb && j != skip && (key & mask) == (prefix & mask);
+      const uint64_t m = __ballot(act);
+      if (m == 0ull) continue;
+      const uint32_t first = __builtin_amdgcn_readlane(bin, (int)__builtin_ctzll(m));
+      if (__ballot(act && bin == first) == m) {  // uniform
+        if (lane == 0) atomicAdd(&h[first], (uint32_t)__popcll(m));
+      } else if (act) {
+        atomicAdd(&h[bin], 1u);
+      }
     }
   }
   __syncthreads();
