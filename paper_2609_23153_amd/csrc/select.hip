@@ -256,9 +256,14 @@ constexpr int kSChunks = kSTile * kSDepth / 2 / 256;  // 16-byte chunks per thre
 __global__ __launch_bounds__(256) void score_kernel(const double* __restrict__ qhat,
                                                    const double* __restrict__ khat, int N,
                                                    int block, int nb,
+                                                   const int32_t* __restrict__ left,
                                                    double* __restrict__ scores) {
   const int bh = blockIdx.z;
   const int i0 = blockIdx.y * kSTile, j0 = blockIdx.x * kSTile;
+  if (left) {  // only tiles with a row that the fused kernel left (count -1)
+    const int i = i0 + (int)(threadIdx.x & (kSTile - 1));
+    if (!__syncthreads_or(i < nb && left[(int64_t)bh * nb + i] < 0)) return;
+  }
   const double* qb = qhat + (int64_t)bh * nb * kHeadDim;
   const double* kb = khat + (int64_t)bh * nb * kHeadDim;
   __shared__ __attribute__((aligned(16))) double As[kSTile * kSStride];
@@ -450,7 +455,7 @@ __device__ __forceinline__ void select_emit(const uint32_t (&hi)[KPL], const uin
 template <int KPL>
 __global__ __launch_bounds__(256) void topk_row_kernel(const double* __restrict__ scores,
                                                        int nb, int rows, int k_all, int kmax,
-                                                       bool k_per_row, Shape cs,
+                                                       bool k_per_row, bool left, Shape cs,
                                                        int32_t* __restrict__ idx,
                                                        int32_t* __restrict__ cnt) {
   __shared__ uint32_t cand[4][3][kWave];  // per wave: candidate hi, lo, index
@@ -458,6 +463,7 @@ __global__ __launch_bounds__(256) void topk_row_kernel(const double* __restrict_
   const int wv = threadIdx.x >> 6;
   const int row = blockIdx.x * 4 + wv;
   if (row >= rows) return;  // uniform per wave
+  if (left && cnt[row] >= 0) return;  // the fused kernel has this row's list
   // Candidate key blocks [jlo, jhi): under a causal window those holding an
   // allowed key of some query of the block (the allowed ranges never move
   // back as the query advances, so the first query's lower end and the last
@@ -536,24 +542,25 @@ __global__ __launch_bounds__(256) void topk_row_kernel(const double* __restrict_
 
 template <int KPL>
 hipError_t launch_topk(const double* scores, int nb, int rows, int k, int kmax, bool k_per_row,
-                       const Shape& cs,
+                       bool left, const Shape& cs,
                        int32_t* idx, int32_t* cnt, hipStream_t stream) {
   topk_row_kernel<KPL><<<(rows + 3) / 4, 256, 0, stream>>>(scores, nb, rows, k, kmax, k_per_row,
-                                                            cs, idx, cnt);
+                                                            left, cs, idx, cnt);
   return hipGetLastError();
 }
 
-// Row top-k over the score matrix with the register tile that fits nb.
+// Row top-k over the score matrix with the register tile that fits nb (left:
+// of the rows whose count is -1).
 hipError_t launch_topk_any(const double* scores, int nb, int rows, int k, int kmax,
-                           bool k_per_row, const Shape& cs, int32_t* idx, int32_t* cnt,
+                           bool k_per_row, bool left, const Shape& cs, int32_t* idx, int32_t* cnt,
                            hipStream_t stream) {
   const int kpl = (nb + kWave - 1) / kWave;
 #define SA_TOPK(n) \
-  if (kpl <= n) return launch_topk<n>(scores, nb, rows, k, kmax, k_per_row, cs, idx, cnt, stream);
+  if (kpl <= n) return launch_topk<n>(scores, nb, rows, k, kmax, k_per_row, left, cs, idx, cnt, stream);
   SA_TOPK(1) SA_TOPK(2) SA_TOPK(4) SA_TOPK(8) SA_TOPK(12) SA_TOPK(16) SA_TOPK(20) SA_TOPK(24)
   SA_TOPK(32)
 #undef SA_TOPK
-  return launch_topk<64>(scores, nb, rows, k, kmax, k_per_row, cs, idx, cnt, stream);
+  return launch_topk<64>(scores, nb, rows, k, kmax, k_per_row, left, cs, idx, cnt, stream);
 }
 
 // ---- fused score + top-k (row mode) ---------------------------------------
@@ -597,7 +604,12 @@ hipError_t launch_topk_any(const double* scores, int nb, int rows, int k, int km
 // unless the gap between the k-th and (k+1)-th score is within 4E; a band of
 // more than 64 blocks (heavy ties), an inconsistent count, or a row outside
 // the bound's range takes the exact path: every candidate rescored in fp64
-// and the selection of the unfused kernel run on the 64-bit keys.
+// and the selection of the unfused kernel run on the 64-bit keys.  Above
+// kFStrideBig blocks such a row is left (its count set to -1) to score_kernel
+// and topk_row_kernel, which a wave alone cannot keep up with: 5 heads x 1744
+// blocks of equal scores take 291 us, 3020 with every row in the fused kernel and
+// 205 with the score matrix alone; where no row is left the two launches add 4
+// us (i.i.d. normal inputs, 5% kept: 211 -> 215).
 constexpr int kFWaves = 8;
 constexpr int kFThreads = kFWaves * kWave;
 constexpr int kFStrideLong = 2384;  // LDS key-row stride = largest nb: 152.6 KB of keys (16 rows)
@@ -731,6 +743,7 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
     Shape cs, int k_all, int kmax, int ntiles, int qtiles, int per_xcd,
     int32_t* __restrict__ idx, int32_t* __restrict__ cnt) {
   constexpr int KPL = (NBP + kWave - 1) / kWave;
+  constexpr bool kLeave = NBP == kFStrideLong;
   static_assert(NBP % 4 == 0 && NBP >= 129, "a key row holds one parked query block, 16-byte aligned");
   __shared__ __align__(16) uint32_t keys[ROWS * NBP];
   __shared__ uint32_t cand[kFWaves][2][kWave];
@@ -935,10 +948,15 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
       KLO = order_key32(flo) - ((double)flo > lo ? 1u : 0u);
       KHI = order_key32(fhi) + ((double)fhi < hi ? 1u : 0u);
     };
+    bool left = false;  // this row's list is left to the kernels of the score matrix
+    auto all_exact = [&]() {
+      if (kLeave) left = true;
+      else exact_row_select<KPL>(qrow, khead, cs, ni, jlo, jhi, k, out);
+    };
     if (k >= jhi - jlo) {
       for (int p = lane; p < k; p += kWave) out[p] = jlo + p;
     } else if (!bounded) {
-      exact_row_select<KPL>(qrow, khead, cs, ni, jlo, jhi, k, out);
+      all_exact();
     } else {
       uint32_t key[KPL];
       uint32_t mk = 0;  // 0: not a candidate (below every score's key)
@@ -1150,12 +1168,12 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
             taken += __popcll(m);
           }
         } else {
-          exact_row_select<KPL>(qrow, khead, cs, ni, jlo, jhi, k, out);
+          all_exact();
         }
       }
     }
     for (int p = k + lane; p < kmax; p += kWave) out[p] = -1;
-    if (lane == 0) cnt[row] = k;
+    if (lane == 0) cnt[row] = left ? -1 : k;
     // (the next row rewrites this wave's cand slots: a wave's LDS accesses
     // complete in order, so the reads above see this row's values)
   }
@@ -1423,7 +1441,7 @@ static hipError_t launch_pool_score(const Shape& s, const void* q, Strides qs, c
   if (e != hipSuccess) return e;
   const int tiles = (s.nb + kSTile - 1) / kSTile;
   score_kernel<<<dim3(tiles, tiles, bh), 256, 0, stream>>>(qhat, khat, s.N, s.block, s.nb,
-                                                           scores);
+                                                           nullptr, scores);
   *scores_out = scores;
   return hipGetLastError();
 }
@@ -1480,6 +1498,16 @@ hipError_t launch_select_row(const Shape& s, const void* q, Strides qs, const vo
     } else {
       if (s.block == 64) SA_FUSED(16, kFStrideLong, 64);
       else SA_FUSED(16, kFStrideLong, 128);
+      // the rows left (none on most inputs): two launches that return at once
+      // where there is nothing to do; the score matrix takes the operands' place
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      double* scores = khat + bh * s.nb * kHeadDim;
+      const int tiles = (s.nb + kSTile - 1) / kSTile;
+      score_kernel<<<dim3(tiles, tiles, bh), 256, 0, stream>>>(qhat, khat, s.N, s.block, s.nb,
+                                                               cnt, scores);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      return launch_topk_any(scores, s.nb, (int)(bh * s.nb), topk, kmax, false, true, s, idx, cnt,
+                             stream);
     }
 #undef SA_FUSED_ROWS
 #undef SA_FUSED
@@ -1489,7 +1517,7 @@ hipError_t launch_select_row(const Shape& s, const void* q, Strides qs, const vo
   hipError_t e = launch_pool_score(s, q, qs, k, ks, ws, &scores, stream);
   if (e != hipSuccess) return e;
   const int rows = s.B * s.H * s.nb;
-  return launch_topk_any(scores, s.nb, rows, topk, kmax, false, s, idx, cnt, stream);
+  return launch_topk_any(scores, s.nb, rows, topk, kmax, false, false, s, idx, cnt, stream);
 }
 
 hipError_t launch_select_head(const Shape& s, const void* q, Strides qs, const void* k,
@@ -1520,7 +1548,7 @@ hipError_t launch_select_head(const Shape& s, const void* q, Strides qs, const v
   Shape unrestricted = s;  // the whole-head mode has no causal window
   unrestricted.causal_chunk = 0;
   unrestricted.causal_window = 0;
-  return launch_topk_any(scores, s.nb, rows, 0, kmax, true, unrestricted, idx, cnt, stream);
+  return launch_topk_any(scores, s.nb, rows, 0, kmax, true, false, unrestricted, idx, cnt, stream);
 }
 
 }  // namespace sa

@@ -497,3 +497,60 @@ def test_launch_order_of_uneven_lists_takes_no_longer():
     a, b = us(even), us(uneven)
     say(f"  equal lists {a:.1f} us, uneven {b:.1f}")
     assert b < 1.7 * a, (a, b)
+
+
+@pytest.mark.parametrize("nb,block", [(1193, 64), (1500, 128), (2384, 64)])
+@pytest.mark.parametrize("causal", [None, (20000, 0)])
+def test_select_rows_left_to_the_score_matrix(nb, block, causal):
+    """Above 1192 blocks, the rows that the on-chip selection cannot decide are
+    taken from the fp64 score matrix: rows of equal scores (zero queries, and
+    -0), of queries past the bound's range and of more than 64 equal key blocks
+    around the k-th, beside rows that it does decide and in groups of their own."""
+    N, k = nb * block - 17, nb // 10
+    g = torch.Generator().manual_seed(nb)
+    q, kk = (torch.randn(1, 2, N, 128, generator=g).to(torch.bfloat16) for _ in range(2))
+    zero = [3, 100, 101] + list(range(160, 320)) + [nb - 1]
+    for i in zero:
+        q[0, 0, i * block:(i + 1) * block] = 0.0 if i % 2 else -0.0
+    kk[0, 1, 64 * block:] = kk[0, 1, 64 * block:65 * block].repeat(nb, 1)[:N - 64 * block]
+    q[0, 1, 5 * block + 3] *= 2.0 ** 70   # past the bound's range
+    idx, cnt = sa.sparse_attn_select(q.to(DEV), kk.to(DEV), k, block=block, causal=causal)
+    idx, cnt = idx.cpu().numpy(), cnt.cpu().numpy()
+    for h in range(2):
+        x, y = widen(q[0, h]), widen(kk[0, h])
+        bp = 10000 * k // nb
+        bp += O.keep_count(bp, nb) < k
+        assert O.keep_count(bp, nb) == k
+        ri, rc = O.select_head(x, y, block, bp) if causal is None else \
+            O.select_causal(x, y, block, bp, *causal)
+        assert np.array_equal(cnt[0, h], rc), h
+        bad = np.nonzero((idx[0, h] != ri).any(axis=1))[0]
+        assert bad.size == 0, (h, bad[:5])
+
+
+def test_select_of_equal_scores_takes_little_longer():
+    """5 heads x 1744 blocks of equal scores: taken from the score matrix it
+    takes about twice the time of i.i.d. normal inputs, 15 times with every row
+    rescored by a wave of the fused kernel."""
+    H, N, k = 5, 1744 * 64, 87
+    g = torch.Generator(device=DEV).manual_seed(2)
+    q, kk = (torch.randn(1, H, N, 128, generator=g, device=DEV).bfloat16() for _ in range(2))
+
+    def us():
+        sa.sparse_attn_select(q, kk, k)
+        best = float("inf")
+        for _ in range(3):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(5):
+                sa.sparse_attn_select(q, kk, k)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 5 * 1e3)
+        return best
+
+    normal = us()
+    q.zero_()
+    equal = us()
+    say(f"  normal {normal:.0f} us, equal scores {equal:.0f}")
+    assert equal < 4 * normal, (normal, equal)
