@@ -440,29 +440,44 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_kernel(Params p) {
 
 }  // namespace
 
+// Both kernels give the same bytes; true where the one of one wave per tile is
+// the faster one (us, this kernel / one wave, lists of 36 tiles of 64 keys).
+//  * Per full round of one tile on every SIMD it gains 0.15 us a listed key
+//    tile, less about 1 us in all for a launch of one round and 6 for 2 to 5:
+//    1024 tiles 92 / 87, 2048 173 / 166, 4096 340 / 324, 12,288 1022 / 949; lists
+//    of 8: 33 / 32, 57 / 63, 106 / 111, 334 / 324.
+//  * A last round of which a share f is filled costs it 1.1 (1 - f) us a listed
+//    key tile more than this kernel, two of whose workgroups share a CU: 1280
+//    tiles 113 / 143, 1536 134 / 146, 3434 293 / 300, 5190 438 / 455.  From 9/10
+//    on it is as good as full (939: 90 / 82).
+//  * A single list takes it twice as long, 1.44 us a block against 0.69, so it
+//    loses where some lists are much longer than the mean, and it is left to
+//    lists that a kmax below the row of key blocks keeps alike (a row top-k).
+//    With kmax = nb (a whole-head budget) the longest may be the whole row: 12
+//    heads x 512 blocks, 36 kept a row but all of one: 637 / 872 us, 2 heads 354 /
+//    737; lengths spread exponentially 1027 / 1170, 2 heads 197 / 371; at a
+//    spread of a third of the mean this kernel's own loss is 3% (813 / 788).
+static bool one_wave_per_tile(const Shape& s, int kmax, int64_t tiles, int cus) {
+  if (kmax >= s.nb) return false;
+  const int64_t slots = 4 * cus, list = (int64_t)kmax * (s.block / kTile);
+  int64_t full = tiles / slots, rest = tiles % slots;
+  if (10 * rest >= 9 * slots) {
+    ++full;
+    rest = 0;
+  }
+  const int64_t fixed = full <= 1 ? 100 : full <= 5 ? 600 : 0;
+  const int64_t partial = rest ? 110 * list * (slots - rest) / slots : 0;
+  return 15 * list * full > fixed + partial;  // in 0.01 us
+}
+
 hipError_t launch_fwd_bf16(const Shape& s, const FwdArgs& a, hipStream_t stream) {
-  // Both kernels give the same bytes.  The one of one wave per tile takes about
-  // 85 us a round of 4 tiles per CU (36 key blocks a tile), 58 us + 30 us x
-  // filled share for a last partial round; this one 96 us for as many tiles, in
-  // proportion.  So 58 of the partial round has to be made up for (us, this
-  // kernel / one wave: 512 tiles 49 / 66, 1024 105 / 97, 1280 123 / 145, 1800
-  // 182 / 167, 4096 354 / 329, 47,280 4200 / 4000).
-  // A single list takes it twice as long, 1.44 us a block against 0.69, so it
-  // loses where some lists are much longer than the mean, and it is left to
-  // lists that a kmax below the row of key blocks keeps alike (a row top-k).
-  // With kmax = nb (a whole-head budget) the longest may be the whole row: 12
-  // heads x 512 blocks, 36 kept a row but all of one: 637 / 872 us, 2 heads 354 /
-  // 737; lengths spread exponentially 1027 / 1170, 2 heads 197 / 371; at a
-  // spread of a third of the mean this kernel's own loss is 3% (813 / 788).
   const int grid = s.B * s.H * ((s.N + kTile - 1) / kTile);
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-  const int full = grid / (4 * cus), rest = grid % (4 * cus);
-  if (a.kmax < s.nb && (rest == 0 || 14 * full + 65 * rest / (4 * cus) > 58))
-    return launch_fwd_bf16_wave(s, a, stream);
+  if (one_wave_per_tile(s, a.kmax, grid, cus)) return launch_fwd_bf16_wave(s, a, stream);
   Params p;
   p.q = static_cast<const uint16_t*>(a.q);
   p.k = static_cast<const uint16_t*>(a.k);

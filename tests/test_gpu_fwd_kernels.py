@@ -2,9 +2,9 @@
 one) give the same bytes, the edge paths of the one-wave kernel meet the oracle,
 and it is not given lists of which one may be far longer than the others.
 
-Every case of the edges is a launch of 1024 tiles (4 per CU of 256 CUs), which the
-rule gives to the one-wave kernel; the same heads computed alone are 16-tile
-launches, which take the four-wave one."""
+Every case of the edges is a launch of 6144 tiles (six on every SIMD of 256
+CUs), which the rule gives to the one-wave kernel; the same heads computed alone
+are launches of 8 or 16, which take the four-wave one."""
 import numpy as np
 import pytest
 import torch
@@ -35,11 +35,15 @@ def _gpu():
     torch.cuda.synchronize()
 
 
-def one_wave(tiles, kmax, nb):
-    """The forward's rule: rounds of 4 tiles per CU and the last one's share,
-    and lists that cannot be the whole row."""
-    full, rest = divmod(tiles, 4 * CUS)
-    return kmax < nb and (rest == 0 or 14 * full + 65 * rest // (4 * CUS) > 58)
+def one_wave(tiles, kmax, nb, block=64):
+    """The forward's rule (0.01 us): full rounds of a tile on every SIMD against
+    what a launch and a partial round cost, and lists that cannot be the whole row."""
+    slots, keys = 4 * CUS, kmax * (block // 64)
+    full, rest = divmod(tiles, slots)
+    if 10 * rest >= 9 * slots:
+        full, rest = full + 1, 0
+    fixed = 100 if full <= 1 else 600 if full <= 5 else 0
+    return kmax < nb and 15 * keys * full > fixed + 110 * keys * (slots - rest) // slots * (rest > 0)
 
 
 def make_lists(kind, B, H, nb, kmax, seed):
@@ -74,12 +78,12 @@ def valid_lists(idx, cnt, nb):
 
 
 def tensors(B, H, N, token_major, seed, qk_scale, growing):
-    g = torch.Generator().manual_seed(seed)
-    x = [torch.randn(B, H, N, 128, generator=g) for _ in range(3)]
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    x = [torch.randn(B, H, N, 128, generator=g, device=DEV) for _ in range(3)]
     x[0] *= qk_scale
     x[1] *= qk_scale
     if growing:  # later keys score higher: the reference maximum keeps rising
-        x[1] *= torch.linspace(0.2, 6, N)[:, None]
+        x[1] *= torch.linspace(0.2, 6, N, device=DEV)[:, None]
     out = []
     for t in x:
         d = torch.empty(B, N, H, 128, dtype=torch.bfloat16, device=DEV).permute(0, 2, 1, 3) \
@@ -88,24 +92,24 @@ def tensors(B, H, N, token_major, seed, qk_scale, growing):
     return out
 
 
-# B * H * ceil(N / 64) = 1024 tiles in each; N of 1000 and 1023: last tile of
+# B * H * ceil(N / 64) = 6144 tiles in each; N of 1000 and 1023: last tile of
 # 40 and 63 rows, 993: of 33 and 449 of 1, whose second half tile is past the
 # end; block 128: N mod 128 = 104, 33 and 1
 CASES = [
     # B, H, N, block, lists, token-major, causal, q and k scale, growing keys
-    (2, 32, 1000, 64, "full", False, None, 1.0, False),
-    (2, 32, 1000, 64, "ragged", True, None, 2.0, False),
-    (1, 64, 1023, 64, "invalid", True, None, 1.0, False),
-    (2, 32, 993, 64, "ragged", False, None, 1.0, True),
-    (2, 64, 449, 64, "invalid", False, None, 2.0, True),
-    (2, 32, 1000, 128, "ragged", True, None, 1.0, True),
-    (1, 64, 993, 128, "invalid", False, None, 2.0, False),
-    (4, 32, 449, 128, "full", True, None, 1.0, False),
-    (2, 32, 1000, 64, "full", True, (100, 0), 1.0, False),
-    (2, 32, 1000, 64, "ragged", False, (100, 1), 2.0, False),
-    (2, 32, 1000, 128, "ragged", True, (333, 2), 1.0, True),
-    (2, 32, 1000, 64, "full", False, (17, 3), 1.0, False),
-    (1, 64, 993, 128, "invalid", True, (64, 1), 1.0, False),
+    (2, 192, 1000, 64, "full", False, None, 1.0, False),
+    (2, 192, 1000, 64, "ragged", True, None, 2.0, False),
+    (1, 384, 1023, 64, "invalid", True, None, 1.0, False),
+    (2, 192, 993, 64, "ragged", False, None, 1.0, True),
+    (2, 384, 449, 64, "invalid", False, None, 2.0, True),
+    (2, 192, 1000, 128, "ragged", True, None, 1.0, True),
+    (1, 384, 993, 128, "invalid", False, None, 2.0, False),
+    (4, 192, 449, 128, "full", True, None, 1.0, False),
+    (2, 192, 1000, 64, "full", True, (100, 0), 1.0, False),
+    (2, 192, 1000, 64, "ragged", False, (100, 1), 2.0, False),
+    (2, 192, 1000, 128, "ragged", True, (333, 2), 1.0, True),
+    (2, 192, 1000, 64, "full", False, (17, 3), 1.0, False),
+    (1, 384, 993, 128, "invalid", True, (64, 1), 1.0, False),
 ]
 
 
@@ -114,7 +118,7 @@ def test_one_wave_kernel_edges(B, H, N, block, kind, token_major, causal, qk_sca
     seed = 31 * N + block + len(kind)
     nb = O.block_count(N, block)
     kmax, tiles = max(2, nb - 2), -(-N // 64)
-    assert one_wave(B * H * tiles, kmax, nb) and not one_wave(tiles, kmax, nb)
+    assert one_wave(B * H * tiles, kmax, nb, block) and not one_wave(tiles, kmax, nb, block)
     q, k, v = tensors(B, H, N, token_major, seed, qk_scale, growing)
     idx, cnt = make_lists(kind, B, H, nb, kmax, seed)
     di, dc = idx.to(DEV), cnt.to(DEV)
@@ -151,7 +155,7 @@ def test_rows_of_equal_values_come_back_exactly(qk_scale):
     them (rounded to bf16), so their roundings cancel: V = 1 gives O = 1, to
     the fp32 sums' 1e-6, which is 1 in bf16.  Sums of the unrounded ones would
     leave a relative error of up to 2^-9."""
-    B, H, N = 2, 32, 1000
+    B, H, N = 2, 192, 1000
     q, k, v = tensors(B, H, N, False, 5, qk_scale, False)
     v.fill_(1.0)
     idx, cnt = make_lists("full", B, H, 16, 13, 6)
