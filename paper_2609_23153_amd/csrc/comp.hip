@@ -651,9 +651,10 @@ hipError_t launch_comp_state(const Shape& s, const CompStateIn& in, float* state
 // Tiles of 128 tokens per comp_out workgroup, 1 to kOutTiles: those for which
 // the most loaded CU does the least, where staging C^T and P_q costs 7 units and
 // a tile 5 (one workgroup of 1, 2, 4, 8 tiles a CU takes 9.5, 14.2, 22.7, 37.6
-// us).  Always 8 -> by the rule, us: 2 heads x 4096 tokens 39 -> 10 (1 tile), 40
-// x 8000 71 -> 60 (3), 12 x 32760 92 -> 79 (4), 40 x 20000 165 -> 153 (5), 40 x
-// 75600 stays at 8 (551); 16 or 32 tiles gain 1% there and lose elsewhere.
+// us).  Always 8 -> by the rule, us: 2 heads x 4096 tokens 39 -> 10 (1 tile), 12
+// x 32760 92 -> 78 (4), 40 x 20000 168 -> 154 (5), 40 x 8000 74 -> 59 (6), 20 x
+// 9250 45 -> 41 (7), 40 x 75600 stays at 8 (553); 16 or 32 tiles gain 1% there
+// and lose elsewhere.
 static int out_tiles(const Shape& s, int cus) {
   const int64_t groups = (int64_t)s.B * s.H * comp_state_chunks(s);
   const int sub = (comp_span(s) + kSub - 1) / kSub;  // tiles of a causal chunk

@@ -186,14 +186,23 @@ def test_comp_causal_full_size_heads():
                           "14B-720P causal")
 
 
-@pytest.mark.parametrize("heads,n", [(1, 130), (2, 4096), (6, 8200), (40, 8000), (12, 32760),
-                                     (40, 20000), (3, 111600), (20, 12345)])
+def out_tiles(groups, span, cus=256):
+    """The library's rule: 128-token tiles per workgroup, of 1 to 8 those for
+    which the most loaded CU does the least (7 units a workgroup, 5 a tile)."""
+    cost = lambda t: -(-groups * -(-(-(-span // 128)) // t) // cus) * (7 + 5 * t)
+    return min(range(8, 0, -1), key=cost)  # a tie to the larger
+
+
+@pytest.mark.parametrize("heads,n,tiles", [
+    (1, 130, 1), (2, 4096, 1), (6, 8200, 2), (20, 3250, 3), (12, 32760, 4), (20, 12345, 4),
+    (40, 20000, 5), (40, 8000, 6), (3, 111600, 6), (20, 9250, 7), (30, 7250, 8)])
 @pytest.mark.parametrize("chunk", [0, 3000])
-def test_comp_out_tiles_per_workgroup(heads, n, chunk):
+def test_comp_out_tiles_per_workgroup(heads, n, tiles, chunk):
     """A workgroup takes 1 to 8 tiles of tokens, by the number of workgroups
-    that makes (1, 1, 2, 3, 4, 5, 6, 8 at 256 CUs without chunks).  A token's
-    output depends on its own inputs and the state alone, so pieces computed
-    by themselves, with one tile each, give the same bytes."""
+    that makes (`tiles` at 256 CUs without chunks).  A token's output depends on
+    its own inputs and the state alone, so pieces computed by themselves, with
+    one tile each, give the same bytes."""
+    assert out_tiles(heads, n) == tiles and out_tiles(heads, 300) == 1
     g = torch.Generator(device=DEV).manual_seed(heads + n)
     rnd = lambda *s: torch.randn(*s, generator=g, device=DEV)
     q, o_s = rnd(1, heads, n, 128).bfloat16(), rnd(1, heads, n, 128).bfloat16()
@@ -215,3 +224,22 @@ def test_comp_out_tiles_per_workgroup(heads, n, chunk):
                                            states[:, :, c].contiguous(), cut(gate), cut(o_s))
             assert torch.equal(part.view(torch.int16), cut(o).view(torch.int16)), (c, a, b)
     say(f"  comp out {heads}x{n}, chunk {chunk}: pieces equal")
+
+
+@pytest.mark.parametrize("n", [6 * 1024 + 5, 7 * 1024, 7 * 1024 + 1, 8 * 1024, 15 * 1024 + 9,
+                               16 * 1024, 16 * 1024 + 1])
+def test_comp_state_sums_its_partials_in_order(n):
+    """A state is the sum, in order, of its 1024-token partials, of which 8 are
+    loaded ahead where there are that many: 7, 8, 9, 16 and 17 of them, whole and
+    ragged.  A piece of 1024 tokens alone is its partial."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    rnd = lambda *s: torch.randn(*s, generator=g, device=DEV)
+    k, v = rnd(1, 3, n, 128).bfloat16(), rnd(1, 3, n, 128).bfloat16()
+    pk = (rnd(3, R, 128) / 11).bfloat16()
+    rope = rnd(n, R // 2, 2)
+    state = sa.sparse_attn_comp_state(k, v, pk, rope)
+    want = torch.zeros_like(state)
+    for a in range(0, n, 1024):
+        cut = lambda t: t[:, :, a:a + 1024].contiguous()
+        want += sa.sparse_attn_comp_state(cut(k), cut(v), pk, rope[a:a + 1024].contiguous())
+    assert torch.equal(state, want)
