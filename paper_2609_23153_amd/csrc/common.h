@@ -90,6 +90,21 @@ __device__ __forceinline__ uint32_t e4m3x4(uint32_t w0, uint32_t w1, float inv) 
   return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(bf16_lo(w1) * inv, bf16_hi(w1) * inv, o, true);
 }
 
+// x summed over the wave, in every lane (DPP rotations within the rows of 16
+// lanes, then lane swaps).
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
+#define SA_ROR(n) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + n, 0xF, 0xF, false)
+  SA_ROR(8);
+  SA_ROR(4);
+  SA_ROR(2);
+  SA_ROR(1);
+#undef SA_ROR
+  const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = p[0] + p[1];
+  const auto q = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return q[0] + q[1];
+}
+
 // Whole-wave reductions through DPP-free cross-lane shuffles.
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll

@@ -229,21 +229,6 @@ __global__ __launch_bounds__(kSortThreads) void sched_scatter_kernel(
   }
 }
 
-// x summed over the wave, in every lane (DPP rotations within the rows of 16
-// lanes, then lane swaps).
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x) {
-#define SA_ROR(n) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + n, 0xF, 0xF, false)
-  SA_ROR(8);
-  SA_ROR(4);
-  SA_ROR(2);
-  SA_ROR(1);
-#undef SA_ROR
-  const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-  x = p[0] + p[1];
-  const auto q = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-  return q[0] + q[1];
-}
-
 // The whole sort in one launch, one workgroup per chunk.  When every list has
 // the same length (row selection without a window) the sorted order is the
 // raster order, which a pass over the lengths shows.  Otherwise a thread

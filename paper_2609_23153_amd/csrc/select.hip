@@ -384,16 +384,9 @@ __device__ __forceinline__ uint32_t kth_largest32(const uint32_t (&v)[KPL], cons
   return prefix;
 }
 
-// Whole-wave sum, in every lane (a wave-uniform value).
-__device__ __forceinline__ int wave_sum_u32(int x) {
-  x += (int)row_ror<8>((uint32_t)x, 0u);
-  x += (int)row_ror<4>((uint32_t)x, 0u);
-  x += (int)row_ror<2>((uint32_t)x, 0u);
-  x += (int)row_ror<1>((uint32_t)x, 0u);
-  const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)x, false, false);
-  x = (int)(a[0] + a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
-  return __builtin_amdgcn_readfirstlane((int)(b[0] + b[1]));
+// Whole-wave sum as a wave-uniform value.
+__device__ __forceinline__ int wave_count(int x) {
+  return __builtin_amdgcn_readfirstlane((int)wave_sum_u32((uint32_t)x));
 }
 
 // The k largest of the wave's member keys (hi, lo words; ties to the lower
@@ -649,7 +642,7 @@ __device__ __forceinline__ uint32_t kth_largest_row(const uint32_t (&key)[KPL], 
   }
   // count(key >= lo) = clo >= k > chi = count(key >= hi)
   uint32_t lo = wave_min_u32(mn) + 1u, hi = wave_max_u32(mx) + 1u;
-  int clo = wave_sum_u32(n), chi = 0;
+  int clo = wave_count(n), chi = 0;
   *exact = clo == k;
   for (int step = 0; !*exact && hi - lo > 1u; ++step) {
     uint32_t mid = lo + ((hi - lo) >> 1);
@@ -662,7 +655,7 @@ __device__ __forceinline__ uint32_t kth_largest_row(const uint32_t (&key)[KPL], 
     int c = 0;
 #pragma unroll
     for (int t = 0; t < KPL; ++t) c += key[t] >= mid;
-    c = wave_sum_u32(c);
+    c = wave_count(c);
     if (c >= k) {
       lo = mid;
       clo = c;
@@ -1114,8 +1107,8 @@ __global__ __launch_bounds__(kFThreads) void score_topk_kernel(
           cin += key[t] > KHI;
           cband += key[t] != 0u && key[t] <= KHI && key[t] >= KLO;
         }
-        cin = wave_sum_u32(cin);
-        cband = wave_sum_u32(cband);
+        cin = wave_count(cin);
+        cband = wave_count(cband);
         if (cband <= kWave && cin <= k && cin + cband >= k) {
           // compact the band's indices; rescore them in fp64, all lanes on
           // one block at a time (lane l: channels 2 l, 2 l + 1)

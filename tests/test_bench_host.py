@@ -65,3 +65,16 @@ def test_traffic_follows_the_summary_only_while_sources_match(tmp_path, monkeypa
     assert bench.measured_traffic("fwd_fp8_kernel", "wan14b_720p") is None
     monkeypatch.setattr(bench, "TRAFFIC_PROFILE", str(tmp_path / "missing.txt"))
     assert bench.measured_traffic("fwd_bf16_kernel", "wan14b_720p") is None
+
+
+def test_forward_kernel_is_the_rule_that_the_library_states():
+    """The roofline's label, at the sizes beside the library's rule."""
+    wave = lambda *a: bench.forward_kernel(*a) == "fwd_bf16_wave_kernel"
+    for tiles, keys in ((1024, 36), (2048, 36), (4096, 36), (12288, 36), (1024, 8), (12288, 8),
+                        (939, 36), (47280, 36)):
+        assert wave(tiles, keys, 1182, 64), (tiles, keys)
+    for tiles, keys in ((2048, 8), (4096, 8), (1280, 36), (1536, 36), (3434, 36), (5190, 36),
+                        (900, 36), (8, 36)):
+        assert not wave(tiles, keys, 1182, 64), (tiles, keys)
+    assert not wave(47280, 1182, 1182, 64)            # a list may be the whole row
+    assert wave(2048, 18, 591, 128) and not wave(2048, 18, 1182, 64)

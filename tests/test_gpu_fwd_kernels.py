@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 import torch
 
+import bench
 import oracle as O
 import paper_2609_23153_amd as sa
 import workloads as W
@@ -36,14 +37,8 @@ def _gpu():
 
 
 def one_wave(tiles, kmax, nb, block=64):
-    """The forward's rule (0.01 us): full rounds of a tile on every SIMD against
-    what a launch and a partial round cost, and lists that cannot be the whole row."""
-    slots, keys = 4 * CUS, kmax * (block // 64)
-    full, rest = divmod(tiles, slots)
-    if 10 * rest >= 9 * slots:
-        full, rest = full + 1, 0
-    fixed = 100 if full <= 1 else 600 if full <= 5 else 0
-    return kmax < nb and 15 * keys * full > fixed + 110 * keys * (slots - rest) // slots * (rest > 0)
+    """The launch goes to the one-wave kernel."""
+    return bench.forward_kernel(tiles, kmax, nb, block, CUS) == "fwd_bf16_wave_kernel"
 
 
 def make_lists(kind, B, H, nb, kmax, seed):

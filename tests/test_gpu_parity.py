@@ -144,8 +144,9 @@ def test_select_extreme_magnitudes(qexp, kexp):
 
 @pytest.mark.parametrize("nb", [584, 585, 1192, 1193])
 def test_select_on_chip_capacity_edges(nb):
-    """Around the on-chip score rows: 584 blocks (two workgroups per CU), 585
-    and 1192 (one), 1193 (the fp64 score matrix in the workspace)."""
+    """Around the strides of the on-chip score rows: 584 and 585 blocks, 1192 and
+    1193 (the workgroups of 16 rows, which leave undecided rows to the score
+    matrix)."""
     g = torch.Generator().manual_seed(nb)
     N = nb * 64 - 17
     q = torch.randn(1, 1, N, 128, generator=g).to(torch.bfloat16)
