@@ -119,7 +119,8 @@ int32_t sparse_attn_keep_count(int32_t keep_bp, int32_t nkb);
  * Row-mode selection with nkb <= 1192 needs
  * B*H*(2048*nkb + 16384*ceil(nkb/32) + 4*nkb) bytes; above that, and in the
  * whole-head mode, room for the fp64 score matrix (8*nkb^2 bytes per head) is
- * part of it.  (Row mode keeps the block scores on chip up to nkb = 2384.) */
+ * part of it.  (Row mode keeps the block scores on chip up to nkb = 2384, but
+ * for rows with heavy ties above 1192.) */
 size_t sparse_attn_workspace_size(const sparse_attn_desc* desc, int32_t op, int32_t kmax);
 
 /*
@@ -202,6 +203,10 @@ int sparse_attn_schedule_static(const sparse_attn_desc* desc, const int32_t* cnt
  * computed exactly (fp32 online softmax, bf16 MFMA products, fp32 accumulation).
  * List entries outside [0, nkb) are skipped and cnt is clamped to [0, kmax];
  * a query block with no valid entry gets O = 0 and LSE = -inf.
+ * The probabilities are rounded to bf16 for the product with V and summed as
+ * rounded.  A query's result is the same bytes whatever else the call holds
+ * (batches, heads, other lists, the launch order): two kernels serve different
+ * launch sizes, with the same arithmetic.
  *  q, k, v  bf16 via desc strides;  o  bf16 out via desc->o_stride
  *  idx/cnt  int32 [B][H][nqb][kmax] and [B][H][nqb], e.g. from
  *           sparse_attn_select; entries need not be ascending, but a block
@@ -367,7 +372,8 @@ int sparse_attn_quant_rows_fp8(const void* x, int64_t rows, int64_t cols, int64_
  * sparse_attn_linear_w8a8: y[m][n] = bf16((sum_k dec(xq[m][k]) dec(wq[n][k]))
  * * sx[m] * sw[n] + bias[n]) with fp32 accumulation on the fp8 matrix cores
  * (the fp32 epilogue is fmaf(acc * sx[m], sw[n], bias[n]), rounded to nearest
- * even bf16).
+ * even bf16).  Every tile size sums over k in the same order, so a token's
+ * result is the same bytes whatever the number of tokens.
  *  xq, sx   activation codes [M][K] (row stride ldx bytes) and scales [M], as
  *           written by sparse_attn_quant_rows_fp8
  *  wq, sw   weight codes [N][K] (row stride ldw bytes) and scales [N]

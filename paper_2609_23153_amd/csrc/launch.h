@@ -35,9 +35,10 @@ __host__ __device__ inline int causal_hi(const Shape& s, int t) {
 
 // ---- selection -----------------------------------------------------------
 // Workspace: qhat [B*H*nb*128] f64 | khat [same] | then, row mode with
-// nb <= 2384, the split operands and norms of the fused kernel (above 1192 it
-// is sized for the scores all the same), otherwise the scores [B*H*nb*nb] f64
-// (whole-head mode: and the radix-select state).
+// nb <= 2384, the split operands and norms of the fused kernel, otherwise the
+// scores [B*H*nb*nb] f64 (whole-head mode: and the radix-select state).  Above
+// 1192 blocks it is sized for the scores, which the rows that the fused kernel
+// leaves are taken from.
 size_t select_workspace_bytes(const Shape& s);       // row mode
 size_t select_head_workspace_bytes(const Shape& s);  // whole-head mode
 hipError_t launch_select_row(const Shape& s, const void* q, Strides qs, const void* k,

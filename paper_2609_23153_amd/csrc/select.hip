@@ -14,7 +14,8 @@
 //            approximation and a rigorous error bound split the key blocks
 //            into certainly kept, certainly dropped and a band between; only
 //            the band is rescored in fp64 (see the comment above
-//            score_topk_kernel)
+//            score_topk_kernel); above kFStrideBig blocks the rows that this
+//            does not decide go through the two launches below
 //   otherwise:
 //   score  : per (batch, head) an fp64 GEMM qhat . khat^T scaled by
 //            1 / (n_i n_j)  -> scores in the workspace
@@ -1402,7 +1403,8 @@ static void launch_pool(const Shape& s, const void* q, Strides qs, const void* k
 }
 
 // Row mode: pooled sums, then either the fused path's split operands and
-// norms (nb <= kFStrideBig) or the score matrix.
+// norms (nb <= kFStrideBig) or the score matrix (up to kFStrideLong the
+// operands lie in its place until the undecided rows take it).
 size_t select_workspace_bytes(const Shape& s) {
   const size_t bh = (size_t)s.B * s.H;
   const size_t pooled = bh * s.nb * kHeadDim * sizeof(double) * 2;
