@@ -457,6 +457,8 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_kernel(Params p) {
 //    heads x 512 blocks, 36 kept a row but all of one: 637 / 872 us, 2 heads 354 /
 //    737; lengths spread exponentially 1027 / 1170, 2 heads 197 / 371; at a
 //    spread of a third of the mean this kernel's own loss is 3% (813 / 788).
+//    (The lengths are on the device: a caller's own lists that differ as much
+//    under a smaller kmax are not told apart.)
 static bool one_wave_per_tile(const Shape& s, int kmax, int64_t tiles, int cus) {
   if (kmax >= s.nb) return false;
   const int64_t slots = 4 * cus, list = (int64_t)kmax * (s.block / kTile);
